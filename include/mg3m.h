@@ -133,7 +133,15 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    of one shape (64x64 comes as 1x1 with kt=16 and 2x2 with
  *                    kt=32), so the tile, waves and kt of a plan string read back
  *                    as an override for the same tile
- *   kt=16|32         reduction depth staged per step (default 16 with a tile)
+ *                    Shapes of the one-tap HWCN loader (HWCN or via=hwcn, N and K
+ *                    multiples of 4, C a multiple of kt, aligned buffers) also have
+ *                    tiles whose fp32 products run as bf16 part products, exact in
+ *                    both operands (a=vec_m_b3 in plan strings), told apart by their
+ *                    waves: 128x128,waves=1x4,kt=32; 128x256,waves=1x8,kt=32;
+ *                    64x256,waves=1x8,kt=64; 64x128,waves=1x4,kt=64 and kt=32;
+ *                    64x64,waves=1x4,kt=32 and kt=64; 32x128,waves=1x4,kt=32.
+ *                    They are not persistent and dma=1 excludes them
+ *   kt=16|32|64      reduction depth staged per step (default 16 with a tile)
  *   split=<n>        share every tile's reduction out over n work-groups per tile
  *                    (1..64, clamped to the tile's k-tiles; 1 = no split)
  *   tail=<n>         the same for the tiles left over after whole rounds of resident
@@ -331,7 +339,9 @@ typedef struct mg3m_plan_info {
     double pad_efficiency;    /* Mg*Ng*Kg / (padded tile volume), in (0, 1] */
     double est_us;            /* the selector's predicted time */
     int layout;               /* MG3M_LAYOUT_* */
-    int a_mode, b_mode;       /* operand loader variant of the main kernel (its template arguments) */
+    int a_mode, b_mode;       /* operand loader variant of the main kernel (its template arguments);
+                                 a_mode 3: the kernel of bf16 part products, for the shapes of b_mode
+                                 6 (3 with dma=0; its patches go straight to registers either way) */
     int e_mode;               /* epilogue store mode */
     int persistent;           /* 1: grid work-groups loop over the dp_tiles whole tiles */
     int via_hwcn;             /* 1: an NCHW call run as HWCN on copies in the workspace (layout, a_mode,

@@ -1,0 +1,467 @@
+// Implicit-GEMM forward convolution of fp32 data on bf16 MFMA, without losing
+// a bit of either operand: every fp32 value is the exact sum of three bf16
+// parts (8 + 8 + 8 significand bits, each the rounded remainder of the last),
+// and a product is taken as the six part products that reach above 2^-24 of
+// it (hh; hm, mh; hl, mm, lh -- the other three are below 2^-24 together).
+// Included by the instantiation files (conv_b3*.hip).
+//
+// Why: fp32 MFMA has a sixteenth of the bf16 rate on this chip, so six bf16
+// MFMAs in place of one fp32 MFMA are 2.67 times as fast at the peaks.  And
+// the sums are more exact: the hh products go to an accumulator of their own,
+// which rounds once per 32 rows of the reduction where the fp32 MFMA rounds
+// every two, and the five small products (2^-8 of hh and less) to a second
+// one, added at the end.  Against 64-bit sums, random data, 4608 rows: 3.5e-7
+// (fp32 MFMA: 8.7e-7); 64 rows: 4.1e-8 (1.0e-7).
+//
+// What bounds it: power, then instruction issue.  v_mfma_f32_16x16x32_bf16 is
+// used because the 32x32x16 form, which reads and writes twice the
+// accumulators per product, ran the chip into its power limit (MFMAs alone on
+// random data: 229 against 372 TFLOPS of fp32 products).  Splitting an operand
+// takes 5.5 vector instructions per element, so the split is done once per
+// work-group for the filter (through LDS) and once per wave for the patches,
+// and is spread between the MFMAs.
+//
+// Range.  A part below 2^-133 is lost, so an element under 2^-110 keeps an
+// absolute precision of 2^-133 only; and an infinity has no finite remainder.
+// A wave checks its finished sums: where one is not finite, or nonzero and
+// under 2^-86 (what the lost parts could reach is then no longer below the
+// sum's own rounding), it computes them again on fp32 MFMA.
+#pragma once
+
+#include "conv_kernel.h"
+
+namespace mg3m {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// W floats at byte offset voff + soff (voff is what the buffer's bound is
+// checked against).
+template <int W>
+__device__ __forceinline__ void bload_w(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, float (&v)[W]) {
+  static_assert(W == 1 || W == 2 || W == 4, "one load");
+  if constexpr (W == 4) {
+    const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = x[i];
+  } else if constexpr (W == 2) {
+    const f32x2 x = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+    v[0] = x[0];
+    v[1] = x[1];
+  } else {
+    v[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+  }
+}
+template <int W>
+__device__ __forceinline__ void bstore_w(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, const float (&v)[W]) {
+  if constexpr (W == 4)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), r, voff, soff, 0);
+  else if constexpr (W == 2)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f32x2{v[0], v[1]}), r, voff, soff, 0);
+  else
+    bstore1(r, voff, soff, v[0]);
+}
+
+// Two values in three bf16 parts each, packed in pairs.
+__device__ __forceinline__ void split2(float a, float b, unsigned (&o)[3]) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    o[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+    if (p < 2) {
+      a -= __builtin_bit_cast(float, o[p] << 16);
+      b -= __builtin_bit_cast(float, o[p] & 0xffff0000u);
+    }
+  }
+}
+
+// Formed here, not sunk to the block of their use (the next stage).
+__device__ __forceinline__ void pin3(unsigned (&o)[3]) { asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2])); }
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): the
+// indices are constants in f, so register arrays stay in registers.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// Geometry.  The WN waves stand side by side along the columns, each with all
+// MT rows and WTN columns, as 16x16 blocks; KT is a multiple of 32, the depth
+// of one MFMA (KS of them per stage).
+template <int MT, int NT, int KT, int WN>
+struct B3Cfg {
+  static constexpr int T = WN * 64;
+  static constexpr int WTN = NT / WN;
+  static constexpr int TM = MT / 16, TN = WTN / 16, KS = KT / 32;
+  // A thread stages AR consecutive rows of one filter column, UA times.
+  static constexpr int A_ROWS = KT * MT / T;
+  static constexpr int AR = A_ROWS < 8 ? A_ROWS : 8;
+  static constexpr int UA = A_ROWS / AR;
+  static_assert(KT % 32 == 0 && KT * MT % T == 0 && T % MT == 0 && (AR == 2 || AR == 4 || AR == 8) &&
+                A_ROWS % AR == 0, "filter stage split");
+  static_assert(TN == 1 || TN == 2 || TN == 4, "columns per lane");
+  // A stage in LDS: for each part, 16-byte chunks of eight consecutive rows of
+  // one filter column, [KT / 8][MT].
+  static constexpr int PLANE = KT / 8 * MT;
+  static constexpr int STAGE = 3 * PLANE;
+  static constexpr int LDS_CHUNKS = 2 * STAGE;
+  static_assert(LDS_CHUNKS * 16 == lds_bytes_for_b3(TileDesc{MT, NT, KT, 1, WN, 0, 0.0}), "LDS size model");
+};
+
+// Stage order: taps inside channel slabs, as the fp32 one-tap kernels.
+struct TapPos {
+  int r, s, c0;
+  __device__ void init(const KArgs& a, int kt, int KT) {
+    const int rs = a.R * a.S, slab = kt / rs, tap = kt - slab * rs;
+    c0 = slab * KT;
+    r = tap / a.S;
+    s = tap - r * a.S;
+  }
+  // to the next stage if `more` (selects, not branches: the main loop's body
+  // stays one basic block, which the interleaving below needs)
+  __device__ void advance(const KArgs& a, int KT, bool more) {
+    const int s1 = s + (more ? 1 : 0);
+    const bool ws = s1 == a.S;
+    const int r1 = r + (ws ? 1 : 0);
+    const bool wr = r1 == a.R;
+    s = ws ? 0 : s1;
+    r = wr ? 0 : r1;
+    c0 += wr ? KT : 0;
+  }
+};
+
+// Smallest magnitude (as float bits) that a finished sum may have without
+// being computed again: 2^-86.
+constexpr unsigned kB3TinyBits = 0x14800000u;
+
+// One tile's product over the k-tiles [kt0, kt0 + nk), handed to store(acc,
+// m0, column in the tile, column n, g4, whether n exists): acc[i][j][e] is row 16*i +
+// 4*g4 + e, column n + j.
+template <int MT, int NT, int KT, int WN, class Store>
+__device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int t, int tile, int kt0, int nk,
+                                                Store&& store) {
+  using C = B3Cfg<MT, NT, KT, WN>;
+  constexpr int TM = C::TM, TN = C::TN, KS = C::KS;
+  const int m0 = (tile % a.tiles_m) * MT, n0 = (tile / a.tiles_m) * NT;
+  const int wn = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  const int g4 = lane >> 4, q = lane & 15;
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
+  const __amdgpu_buffer_rsrc_t wr = make_rsrc(a.w, a.w_bytes);
+
+  // filter: thread t takes column m0 + t % MT, AR rows of the stage from AR*(t / MT)
+  const int am = m0 + t % MT, ak = t / MT * C::AR;
+  const unsigned avoff = (am < a.Mg) ? 4u * (unsigned)(am + ak * a.K) : kOOB;
+  unsigned* const aslot = reinterpret_cast<unsigned*>(lds) + 4 * ((ak >> 3) * MT + t % MT) + (ak & 7) / 2;
+  // patches: this lane's TN consecutive columns, all of one pixel (N % 4 == 0),
+  // and rows 8*g4 .. 8*g4+7 of each 32: its part of the MFMA's operand, so
+  // the patches never go through LDS (no other wave of the group needs them)
+  const int col = wn * C::WTN + q * TN, n = n0 + col;
+  const bool col_ok = n < a.Ng;
+  const int pix = n / a.N, b = n - pix * a.N, ho = pix / a.Wo;
+  const int ih0 = ho * a.sh - a.ph, iw0 = (pix - ho * a.Wo) * a.sw - a.pw;
+  const int bbase4 = 4 * (((ih0 * a.W + iw0) * a.C + 8 * g4) * a.N + b);
+  const unsigned N4 = 4u * (unsigned)a.N, K4 = 4u * (unsigned)a.K;
+  const int tap_w4 = 4 * a.C * a.N, tap_h4 = a.W * tap_w4;
+
+  float fa[C::UA][C::AR];            // loaded, not yet split
+  float fb[8][TN];
+  u32x4 bf[2][TN][3];                // patch fragments of this k-step and the next
+  unsigned ap[C::UA][C::AR / 2][3];  // split filter rows on their way to LDS
+
+  // Where the next loads go.  Patches are loaded two k-steps ahead, the filter
+  // two stages ahead.
+  TapPos pa, pb;
+  unsigned bv, as, bs;
+  auto place_a = [&]() { as = (unsigned)((pa.r * a.S + pa.s) * a.C + pa.c0) * K4; };
+  auto place_b = [&](bool live, int ks) {
+    const bool ok = live & col_ok & ((unsigned)(ih0 + pb.r) < (unsigned)a.H) & ((unsigned)(iw0 + pb.s) < (unsigned)a.W);
+    const unsigned at = (unsigned)(bbase4 + pb.r * tap_h4 + pb.s * tap_w4);
+    bv = ok ? at : kOOB;
+    bs = (unsigned)(pb.c0 + 32 * ks) * N4;
+  };
+  auto load_a = [&](int u, int i) {
+    float v[1];
+    bload_w<1>(wr, avoff, as + (unsigned)(u * (C::T / MT) * C::AR + i) * K4, v);
+    fa[u][i] = v[0];
+  };
+  auto load_b = [&](int i) { bload_w<TN>(xr, bv, bs + (unsigned)i * N4, fb[i]); };
+
+  // The split work in pieces of two rows of one column.
+  constexpr int ITB = 4 * TN;                          // per k-step
+  constexpr int ITA = C::UA * C::AR / 2;               // per stage
+  static_assert(ITA % KS == 0, "the filter's pieces spread evenly over the k-steps");
+  constexpr int IT = ITB + ITA / KS;
+  auto split_b = [&](int it, int nxt) {
+    const int p = it / TN, j = it % TN;
+    unsigned o[3];
+    split2(fb[2 * p][j], fb[2 * p + 1][j], o);
+    pin3(o);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) bf[nxt][j][k][p] = o[k];
+  };
+  auto split_a = [&](int it, int buf) {
+    const int u = it / (C::AR / 2), p = it % (C::AR / 2);
+    split2(fa[u][2 * p], fa[u][2 * p + 1], ap[u][p]);
+    pin3(ap[u][p]);
+    if (p == C::AR / 2 - 1) {
+      unsigned* const d = aslot + buf * C::STAGE * 4 + u * (C::T / MT) * C::AR / 8 * MT * 4;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if constexpr (C::AR == 8)
+          *reinterpret_cast<u32x4*>(d + k * C::PLANE * 4) = u32x4{ap[u][0][k], ap[u][1][k], ap[u][2][k], ap[u][3][k]};
+        else if constexpr (C::AR == 4)
+          *reinterpret_cast<u32x2*>(d + k * C::PLANE * 4) = u32x2{ap[u][0][k], ap[u][1][k]};
+        else
+          d[k * C::PLANE * 4] = ap[u][0][k];
+      }
+    }
+  };
+  auto reload_b = [&](int it) {
+    if (it % TN == TN - 1) {
+      load_b(2 * (it / TN));
+      load_b(2 * (it / TN) + 1);
+    }
+  };
+  auto reload_a = [&](int it) {
+    load_a(it / (C::AR / 2), 2 * (it % (C::AR / 2)));
+    load_a(it / (C::AR / 2), 2 * (it % (C::AR / 2)) + 1);
+  };
+
+  f32x4 acc[TM][TN], lo[TM][TN];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = lo[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+
+  // One k-step: its NM MFMAs, row block by row block; each block's filter
+  // fragments are read from LDS as the block before it uses a part for the
+  // last time (part h has three products, m two, l one).  Between the MFMAs,
+  // in even steps: the split of the next k-step's patches and of a KS-th of
+  // the next stage's filter, and into the registers that this frees the loads
+  // of the k-step (stage) after it.
+  constexpr int PER = TN * 6, NM = TM * PER;
+  const int abase = g4 * MT + q;
+  auto kstep = [&](auto buf_c, auto ks_c) {
+    constexpr int buf = decltype(buf_c)::value, ks = decltype(ks_c)::value, cur = (buf * KS + ks) & 1;
+    const u32x4* const As = lds + buf * C::STAGE + ks * 4 * MT;
+    bf16x8 av[3];
+    auto read = [&](int i, int p) { av[p] = __builtin_bit_cast(bf16x8, As[p * C::PLANE + i * 16 + abase]); };
+    read(0, 0);
+    read(0, 1);
+    read(0, 2);
+    constexpr int PA[6] = {0, 0, 0, 1, 1, 2}, PX[6] = {0, 1, 2, 1, 0, 0};
+    static_for<IT>([&](auto ic) {
+      constexpr int it = decltype(ic)::value;
+      constexpr int ma = it * NM / IT, mb = (it + 1) * NM / IT;
+      if constexpr (it < ITB) split_b(it, cur ^ 1);
+      else split_a(ks * (ITA / KS) + it - ITB, buf ^ 1);
+      static_for<mb - ma>([&](auto mc) {
+        constexpr int m = ma + decltype(mc)::value, i = m / PER, k = m % PER / TN, j = m % TN;
+        f32x4& d = k == 0 ? acc[i][j] : lo[i][j];
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[PA[k]], __builtin_bit_cast(bf16x8, bf[cur][j][PX[k]]), d, 0, 0, 0);
+        if constexpr (i + 1 < TM && j == TN - 1 && (k == 2 || k == 4 || k == 5)) read(i + 1, PA[k]);
+      });
+      // alternate them one MFMA to a few vector instructions: two waves per
+      // SIMD alone do not fill the MFMA pipe if each runs its split in a block
+      static_for<mb - ma>([&](auto) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, (11 + mb - ma - 1) / (mb - ma), 0);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (it < ITB) reload_b(it);
+      else reload_a(ks * (ITA / KS) + it - ITB);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // The buffer that the previous stage consumed, filled with NaN (debug build).
+  auto poison = [&](int buf) {
+    if constexpr (MG3M_LDS_POISON != 0) {
+      for (int i = t; i < C::STAGE; i += C::T) lds[buf * C::STAGE + i] = u32x4{~0u, ~0u, ~0u, ~0u};
+      __syncthreads();
+    }
+  };
+
+  // Stages go in pairs, one per LDS buffer, KS k-steps each.  Past the last
+  // one the patch columns are out of range and the filter address stays.
+  pa.init(a, kt0, KT);
+  pb = pa;
+  place_a();
+#pragma unroll
+  for (int it = 0; it < ITA; ++it) reload_a(it);
+  place_b(true, 0);
+#pragma unroll
+  for (int it = 0; it < ITB; ++it) reload_b(it);
+#pragma unroll
+  for (int it = 0; it < ITA; ++it) split_a(it, 0);
+#pragma unroll
+  for (int it = 0; it < ITB; ++it) split_b(it, 0);
+  pa.advance(a, KT, nk > 1);
+  place_a();
+#pragma unroll
+  for (int it = 0; it < ITA; ++it) reload_a(it);
+  if constexpr (KS == 1) pb = pa;
+  place_b(KS > 1 || nk > 1, KS > 1 ? 1 : 0);
+#pragma unroll
+  for (int it = 0; it < ITB; ++it) reload_b(it);
+  __syncthreads();
+  auto stage = [&](int it, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    poison(buf ^ 1);
+    pa.advance(a, KT, it + 2 < nk);
+    place_a();
+    static_for<KS>([&](auto ks_c) {
+      // k-step ks of stage it loads the patches two k-steps on
+      constexpr int ks = decltype(ks_c)::value, step = ks + 2;
+      if constexpr (step % KS == 0) pb.advance(a, KT, it + step / KS < nk);
+      place_b(it + step / KS < nk, step % KS);
+      __builtin_amdgcn_sched_barrier(0);
+      kstep(buf_c, ks_c);
+    });
+    __syncthreads();
+  };
+  for (int it = 0; it < nk; it += 2) {
+    stage(it, std::integral_constant<int, 0>{});
+    if (it + 1 < nk) stage(it + 1, std::integral_constant<int, 1>{});
+  }
+  unsigned tiny = 0xffffffffu;
+  float big = 0.f;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      acc[i][j] += lo[i][j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        big += __builtin_fabsf(acc[i][j][e]);                    // infinite or NaN if any is
+        tiny = min(tiny, __builtin_bit_cast(unsigned, acc[i][j][e]) * 2u - 1u);   // zeros wrap to the maximum
+      }
+    }
+  const bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u);
+  if (MG3M_LDS_POISON == 0 && __ballot(again) != 0) {
+    // This wave's part again, on fp32 MFMA, both operands straight from
+    // memory: step k of 32 rows takes rows 8*g + k of each lane group g, the
+    // rows that the lanes' patches hold.
+    clear();
+    pb.init(a, kt0, KT);
+    const unsigned fvoff = 4u * (unsigned)(8 * g4 * a.K + m0 + q);
+    for (int it = 0; it < nk; ++it) {
+#pragma unroll 1
+      for (int ks = 0; ks < KS; ++ks) {
+        place_b(true, ks);
+#pragma unroll
+        for (int k = 0; k < ITB; ++k) reload_b(k);
+        const unsigned fs = (unsigned)((pb.r * a.S + pb.s) * a.C + pb.c0 + 32 * ks) * K4;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            float f[1];
+            bload_w<1>(wr, m0 + i * 16 + q < a.Mg ? fvoff + 64u * i : kOOB, fs + (unsigned)k * K4, f);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[0], fb[k][j], acc[i][j], 0, 0, 0);
+          }
+        }
+      }
+      pb.advance(a, KT, it + 1 < nk);
+    }
+  }
+  store(acc, m0, col, n, g4, col_ok);
+}
+
+// Schedule and tails as conv_igemm_f32: whole tiles grouped per XCD, then the
+// tail work-groups, whose pieces (split, or stream-K runs of up to two) leave
+// tile-local partials for the tail reduction.
+template <int MT, int NT, int KT, int WN, bool FUSE>
+__global__ __launch_bounds__(WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
+void conv_igemm_b3(KArgs a) {
+  using C = B3Cfg<MT, NT, KT, WN>;
+  constexpr int TM = C::TM, TN = C::TN;
+  __shared__ __attribute__((aligned(16))) u32x4 lds[C::LDS_CHUNKS];
+
+  if ((int)blockIdx.x >= a.dp_tiles) {
+    const int w = tail_wg(a, blockIdx.x - a.dp_tiles);
+    TailRun run = tail_run(a, w);
+    for (;;) {
+      int rel, kt0, nk;
+      tail_piece(a, run, &rel, &kt0, &nk);
+      int t = threadIdx.x;
+      asm volatile("" : "+v"(t));
+      const __amdgpu_buffer_rsrc_t pr = make_rsrc(a.ws + tail_slot(w, rel) * (MT * NT), MT * NT * 4);
+      tile_product_b3<MT, NT, KT, WN>(
+          a, lds, t, a.dp_tiles + rel, kt0, nk, [&](f32x4 (&acc)[TM][TN], int, int col, int, int g4, bool) {
+            const unsigned lane_b = 4u * (unsigned)(4 * g4 * NT + col);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                float v[TN];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) v[j] = acc[i][j][e];
+                bstore_w<TN>(pr, lane_b, 4u * ((i * 16 + e) * NT), v);
+              }
+          });
+      run.it += nk;
+      if (run.it >= run.end) return;
+      __syncthreads();   // the next piece restages the LDS buffers
+    }
+  }
+  const int tile = xcd_group(blockIdx.x, a.dp_tiles);
+  tile_product_b3<MT, NT, KT, WN>(
+      a, lds, threadIdx.x, tile, 0, a.k_tiles, [&](f32x4 (&acc)[TM][TN], int m0, int, int n, int g4, bool col_ok) {
+        const __amdgpu_buffer_rsrc_t yr = make_rsrc(a.y, a.y_bytes);
+        const bool has_add = FUSE && a.add != nullptr;
+        const __amdgpu_buffer_rsrc_t ar = make_rsrc(has_add ? a.add : a.y, a.y_bytes);
+        unsigned rs4 = 4u * (unsigned)a.mstride;
+        asm volatile("" : "+s"(rs4));
+        const int row_l = m0 + 4 * g4, rows_left = a.Mg - row_l;
+        const unsigned voff = 4u * (unsigned)(out_colbase<kHWCN>(a, n) + row_l * a.mstride);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool ok = col_ok & (i * 16 + e < rows_left);
+            const unsigned off = ok ? voff + (unsigned)(i * 16 + e) * rs4 : kOOB;
+            float v[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) v[j] = acc[i][j][e];
+            if constexpr (FUSE) {
+              float d[TN];
+              if (has_add) {
+                bload_w<TN>(ar, off, 0u, d);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) v[j] += d[j];
+              }
+              if (a.relu != 0) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                  if (v[j] < 0.f) v[j] = 0.f;     // NaN kept
+              }
+            }
+            bstore_w<TN>(yr, off, 0u, v);
+          }
+      });
+}
+
+template <bool FUSE, int TI>
+constexpr KernelFn b3_kernel_at() {
+  constexpr TileDesc d = kTilesB3[TI];
+  return &conv_igemm_b3<d.mt, d.nt, d.kt, d.wn, FUSE>;
+}
+template <bool FUSE, int... TI>
+KernelFn pick_b3(int tile, std::integer_sequence<int, TI...>) {
+  KernelFn fn = nullptr;
+  ((fn = (tile == TI ? b3_kernel_at<FUSE, TI>() : fn)), ...);
+  return fn;
+}
+
+}  // namespace mg3m

@@ -182,11 +182,11 @@ int launch_conv(const Plan& p, const KArgs& a, void* stream, std::string* err, v
   }
   // stream-K runs need the kernel's loop over pieces; other kernels take one
   // piece per work-group
-  if (p.tail_wgs > 0 && p.sk_s == 0 && (p.acc64 || !tail_runs_multi(p.b_mode))) {
+  if (p.tail_wgs > 0 && p.sk_s == 0 && (p.acc64 || !(p.b3 || tail_runs_multi(p.b_mode)))) {
     *err = "internal: stream-K tail plan for a kernel without multi-piece runs";
     return MG3M_ERR_PLAN;
   }
-  if (p.persist && (p.acc64 || p.tail_wgs != 0 || p.grid > p.dp_tiles)) {
+  if (p.persist && (p.acc64 || p.b3 || p.tail_wgs != 0 || p.grid > p.dp_tiles)) {
     *err = "internal: persistent plans take whole tiles of the fp32 kernel only";
     return MG3M_ERR_PLAN;
   }
@@ -196,6 +196,7 @@ int launch_conv(const Plan& p, const KArgs& a, void* stream, std::string* err, v
     return MG3M_ERR_PLAN;
   }
   KernelFn fn = p.persist ? (fused ? conv_kernel_pt_fused(p.variant, p.tile) : conv_kernel_pt(p.variant, p.tile))
+                : p.b3    ? (fused ? conv_kernel_b3_fused(p.tile) : conv_kernel_b3(p.tile))
                 : p.acc64 ? kernel64_for(p.variant, p.tile)
                           : (fused ? kernel_fused_for(p.variant, p.tile) : kernel_for(p.variant, p.tile));
   if (fn == nullptr) {

@@ -15,6 +15,9 @@ enum Layout : int { kHWCN = 0, kNCHW = 1 };
 //   A (filter):        kAVecM   16-byte vectors along OC   (HWCN, K % 4 == 0)
 //                      kAVecK   16-byte vectors along Kg   (NCHW, Kg % 4 == 0)
 //                      kAScalar single elements            (any)
+//                      kAVecMB3 not a loader of the fp32 kernels: the kernel of
+//                               conv_b3.h (products as bf16 parts), which takes
+//                               the shapes of kBVecNTap with C % 32 == 0
 //   B (input patches): kBVecNTap 16-byte vectors along the batch, one filter tap
 //                               per staged slab (HWCN, N % 4 == 0, C % kt == 0)
 //                      kBVecN   16-byte vectors along the batch (HWCN, N % 4 == 0)
@@ -25,7 +28,7 @@ enum Layout : int { kHWCN = 0, kNCHW = 1 };
 //                      kBVecWTap the same with one filter tap per staged slab of
 //                               channels (NCHW, C % kt == 0; the filter is first
 //                               copied to [R][S][C][K] and read by kAVecM)
-enum AMode : int { kAVecM = 0, kAVecK = 1, kAScalar = 2 };
+enum AMode : int { kAVecM = 0, kAVecK = 1, kAScalar = 2, kAVecMB3 = 3 };
 enum BMode : int { kBVecN = 0, kBVecC = 1, kBScalar = 2, kBVecNTap = 3, kBVecW = 4, kBVecWTap = 5,
                    kBVecNTapDma = 6 };
 // The loader pairs that are instantiated.
@@ -152,6 +155,23 @@ inline constexpr TileDesc kTiles64[kNumTiles64] = {
     {64, 64, 16, 2, 2, 74, 0.64},      // 8: four 32x32 waves
 };
 
+// Tile menu of the kernel that takes fp32 products as bf16 part products
+// (conv_b3.h), one-tap HWCN shapes only.  regs as above; eff is the fraction of
+// its peak (bf16 MFMA / 6) that the model charges.
+constexpr int kNumTilesB3 = 8;
+inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
+    {128, 128, 32, 1, 4, 254, 0.575},                 // 0
+    {128, 256, 32, 1, 8, 244, 0.61},                  // 1: eight waves sharing one filter tile
+    {64, 256, 64, 1, 8, 185, 0.50},                   // 2: 64 output channels
+    {64, 128, 64, 1, 4, 187, 0.43},                   // 3
+    {64, 128, 32, 1, 4, 178, 0.43},                   // 4
+    {64, 64, 32, 1, 4, 114, 0.62, 0, 0, 0.64},        // 5
+    {64, 64, 64, 1, 4, 123, 0.40},                    // 6
+    {32, 128, 32, 1, 4, 131, 0.39},                   // 7: small layers
+};
+// LDS bytes: two stages of the filter in three bf16 parts.
+constexpr int lds_bytes_for_b3(const TileDesc& t) { return 2 * 3 * 2 * t.kt * t.mt; }
+
 // Largest tensor the kernels address: byte offsets are 32-bit and 0xFFFFFFC0
 // is reserved as the out-of-range offset that reads as zero.
 constexpr long long kMaxTensorBytes = 0xFFFFFFC0LL;
@@ -171,6 +191,7 @@ constexpr long long kMaxTensorBytes = 0xFFFFFFC0LL;
 struct Plan {
   int layout;
   int acc64;                // 1: the fp64-accumulating kernel (tile indexes kTiles64)
+  int b3;                   // 1: the kernel of bf16 part products (tile indexes kTilesB3)
   int tile;                 // index into kTiles (kTiles64 when acc64)
   TileDesc t;
   int k_tiles;              // ceil(Kg / kt)
@@ -292,6 +313,11 @@ KernelFn conv_kernel_nchw_tap_fused(int tile);      // conv_nchw_tap_fused.hip
 KernelFn conv_kernel64_hwcn_vecn_tap(int tile);
 KernelFn conv_kernel64_hwcn(int variant, int tile);
 KernelFn conv_kernel64_nchw(int variant, int tile);
+
+// Kernels of bf16 part products by tile, plain and with the fused output
+// stage: conv_b3*.hip.
+KernelFn conv_kernel_b3(int tile);
+KernelFn conv_kernel_b3_fused(int tile);
 
 // Kernel launchers (conv_launch.hip, pool.hip).
 // start / stop: hipEvent_t handles (or null) that take the main kernel's own

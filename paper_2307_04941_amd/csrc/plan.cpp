@@ -27,6 +27,7 @@ constexpr int kCUs = 256;                    // MI355X: 8 XCDs x 32 CUs
 constexpr double kClockHz = 2.4e9;
 constexpr double kFlopPerClkCU = 256.0;      // fp32 MFMA: 4 SIMDs x 64 flop/clk
 constexpr double kFlopPerClkCU64 = 128.0;    // fp64 MFMA: 4 SIMDs x 32 flop/clk
+constexpr double kFlopPerClkCUB3 = 4096.0 / 6;   // bf16 MFMA: 4 SIMDs x 1024 flop/clk, six products for one
 constexpr int kLdsBytesPerCU = 160 * 1024;
 constexpr int kRegsPerLane = 512;            // unified VGPR + AGPR file per SIMD lane
 constexpr int kMaxWavesPerSimd = 8;
@@ -38,6 +39,8 @@ constexpr double kStreamBytesPerS = 4.0e12;
 constexpr double kLaunchUs = 3.0;
 constexpr double kRoundUs = 2.0;
 constexpr double kUtilBase = 0.5, kUtilPerWave = 0.1;
+constexpr double kUtilBaseB3 = 0.5, kUtilPerWaveB3 = 0.25;   // the kernel of bf16 part products: two waves fill it
+constexpr double kStepUsB3 = 0.6;             // its k-step of 32 rows with one work-group on a CU (load, split, MFMA)
 // Persistent plans (conv_igemm_f32_pt), measured on MI355X against the same
 // tile's data-parallel plan: its main loop (run-time LDS buffer parity, one
 // copy of the stage code) runs at 0.92 of the tile's rate on deep reductions
@@ -58,8 +61,15 @@ constexpr double kNchwStridedFactor = 0.6;
 
 long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
-const TileDesc& tile_desc(bool acc64, int i) { return acc64 ? kTiles64[i] : kTiles[i]; }
-int lds_bytes(const TileDesc& t, bool acc64) { return (acc64 || t.m16) ? lds_bytes_for64(t) : lds_bytes_for(t); }
+// The kernel families, each with a tile menu.
+enum Family { kF32 = 0, kF64 = 1, kB3 = 2 };
+
+const TileDesc& tile_desc(Family f, int i) { return f == kF64 ? kTiles64[i] : f == kB3 ? kTilesB3[i] : kTiles[i]; }
+int num_tiles(Family f) { return f == kF64 ? kNumTiles64 : f == kB3 ? kNumTilesB3 : kNumTiles; }
+int lds_bytes(const TileDesc& t, Family f) {
+  return f == kB3 ? lds_bytes_for_b3(t) : (f == kF64 || t.m16) ? lds_bytes_for64(t) : lds_bytes_for(t);
+}
+Family family(const Plan& p) { return p.b3 ? kB3 : p.acc64 ? kF64 : kF32; }
 
 // Registers of the kernel a plan runs: the persistent kernel's with its
 // patch loader, else the tile's (tuned loader).
@@ -70,12 +80,12 @@ int kernel_regs(const TileDesc& t, int persist_variant) {
 
 // Work-groups of this tile resident on one CU, limited by LDS and registers
 // (persist_variant: the loader variant of a persistent plan, else -1).
-int resident_wgs(const TileDesc& t, bool acc64, int persist_variant = -1) {
+int resident_wgs(const TileDesc& t, Family f, int persist_variant = -1) {
   const int waves = t.wm * t.wn;
   const int regs = (kernel_regs(t, persist_variant) + 7) / 8 * 8;
   const int waves_per_simd = std::min(kMaxWavesPerSimd, kRegsPerLane / regs);
   const int by_regs = std::max(1, 4 * waves_per_simd / waves);
-  const int by_lds = std::max(1, kLdsBytesPerCU / lds_bytes(t, acc64));
+  const int by_lds = std::max(1, kLdsBytesPerCU / lds_bytes(t, f));
   return std::min(by_regs, by_lds);
 }
 
@@ -173,8 +183,8 @@ int parse_override(const char* text, Override* o, std::string* err) {
       o->split = (int)v;
     } else if (key == "kt") {
       long v = std::strtol(val.c_str(), &tail, 10);
-      if (tail == val.c_str() || *tail != 0 || (v != 16 && v != 32)) {
-        *err = "plan override: kt must be 16 or 32";
+      if (tail == val.c_str() || *tail != 0 || (v != 16 && v != 32 && v != 64)) {
+        *err = "plan override: kt must be 16, 32 or 64";
         return MG3M_ERR_PLAN;
       }
       o->kt = (int)v;
@@ -235,10 +245,12 @@ long long tail_pieces(const Plan& p) {
 
 // Fill the shape-dependent parts of a plan for one (tile, schedule, param)
 // choice.  Returns false when the choice does not apply to the shape.
-bool shape_plan(const ConvShape& s, bool acc64, int tile, int sched, long long param, Plan* p) {
-  const TileDesc& t = tile_desc(acc64, tile);
+bool shape_plan(const ConvShape& s, Family f, int tile, int sched, long long param, Plan* p) {
+  const TileDesc& t = tile_desc(f, tile);
+  const bool acc64 = f == kF64;
   p->layout = s.layout;
   p->acc64 = acc64 ? 1 : 0;
+  p->b3 = f == kB3 ? 1 : 0;
   p->tile = tile;
   p->t = t;
   p->k_tiles = (int)cdiv(s.Kg, t.kt);
@@ -253,7 +265,7 @@ bool shape_plan(const ConvShape& s, bool acc64, int tile, int sched, long long p
   } else if ((sched == kSplitTail && param > 1) || sched == kStreamK) {
     // whole rounds of resident work-groups run unsplit (none if the tiles do
     // not fill one round: then every tile is shared out)
-    const long long slots = (long long)kCUs * resident_wgs(t, acc64);
+    const long long slots = (long long)kCUs * resident_wgs(t, f);
     dp = tiles / slots * slots;
     tail = tiles - dp;
   }
@@ -294,7 +306,7 @@ bool shape_plan(const ConvShape& s, bool acc64, int tile, int sched, long long p
   p->sk_r = (int)r;
   p->split = tail > 0 ? (int)cdiv(wgs, tail) : 1;
   p->grid = p->persist ? std::min<long long>(dp, (long long)kCUs * param) : dp + wgs;
-  p->lds_bytes = lds_bytes(t, acc64);
+  p->lds_bytes = lds_bytes(t, f);
   const double padded = (double)p->tiles_m * t.mt * (double)p->tiles_n * t.nt *
                         (double)p->k_tiles * t.kt;
   p->pad_eff = (double)s.Mg * (double)s.Ng * (double)s.Kg / padded;
@@ -314,20 +326,23 @@ bool shape_plan(const ConvShape& s, bool acc64, int tile, int sched, long long p
 // partials) once; the tail reduction adds its traffic and a second launch.
 double predict_us(const ConvShape& s, const Plan& p) {
   const TileDesc& t = p.t;
-  const int occ = resident_wgs(t, p.acc64, p.persist ? p.variant : -1);
-  const double rate = p.acc64 ? kFlopPerClkCU64 : kFlopPerClkCU;
+  const int occ = resident_wgs(t, family(p), p.persist ? p.variant : -1);
+  const double rate = p.acc64 ? kFlopPerClkCU64 : p.b3 ? kFlopPerClkCUB3 : kFlopPerClkCU;
   const double tile_flops = 2.0 * t.mt * t.nt * (double)t.kt;
   const bool multitap = s.R * s.S > 1 && s.C >= 2 * t.kt;
   auto phase = [&](long long wgs, int k_tiles) {
     if (wgs <= 0) return 0.0;
     const long long per_cu = cdiv(wgs, kCUs);
     const double waves_per_simd = (double)std::min<long long>(per_cu, occ) * t.wm * t.wn / 4.0;
-    const double util = std::min(1.0, kUtilBase + kUtilPerWave * waves_per_simd);
+    const double util = p.b3 ? std::min(1.0, kUtilBaseB3 + kUtilPerWaveB3 * waves_per_simd)
+                             : std::min(1.0, kUtilBase + kUtilPerWave * waves_per_simd);
     const double eff = t.eff * variant_factor(p.variant) * util * (multitap ? t.eff_multitap : 1.0) *
                        (p.persist ? kPersistEff : 1.0) *
                        (s.layout == kNCHW && p.b_mode == kBVecW && s.sw > 1 ? kNchwStridedFactor : 1.0);
-    return (double)per_cu * tile_flops * k_tiles / (rate * kClockHz * eff) * 1e6 +
-           (p.persist ? 1.0 : (double)cdiv(per_cu, occ)) * kRoundUs;
+    double us = (double)per_cu * tile_flops * k_tiles / (rate * kClockHz * eff) * 1e6;
+    // few work-groups: no faster than the chain of their k-steps
+    if (p.b3) us = std::max(us, (double)cdiv(per_cu, occ) * k_tiles * t.kt / 32 * kStepUsB3);
+    return us + (p.persist ? 1.0 : (double)cdiv(per_cu, occ)) * kRoundUs;
   };
   const int run_k = p.tail_wgs > 0 ? p.sk_q + (p.sk_r > 0 ? 1 : 0) : 0;
   const double t_comp = phase(p.dp_tiles, p.k_tiles) + phase(p.tail_wgs, run_k);
@@ -451,16 +466,21 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
   const int splits[] = {2, 3, 4, 6, 8, 16};
   // via: an NCHW call run as HWCN on 16-byte aligned copies of x, w and y in
   // the workspace, the layout changed on the way in and out (layout.hip)
-  auto consider_one = [&](int ti, int sched, long long sp, bool via) {
+  auto consider_one = [&](Family f, int ti, int sched, long long sp, bool via) {
     Plan c{};
     ConvShape sv = s;
     if (via) sv.layout = kHWCN;
-    if (!shape_plan(sv, acc64, ti, sched, sp, &c)) return;
+    if (!shape_plan(sv, f, ti, sched, sp, &c)) return;
     // the one-tap HWCN loaders load straight into LDS unless the override says
     // otherwise, except in the fp64-accumulating kernels and the 16-row tile,
     // which stage through VGPRs
     const bool dma_ok = !c.acc64 && !c.t.m16;
     choose_modes(sv, via || x16, via || w16, via || y16, &c, dma_ok && o.dma != 0);
+    if (c.b3) {
+      // the one-tap HWCN shapes with C a multiple of its kt, 16-byte aligned output
+      if ((c.variant != kVarHwcnVecNTapDma && c.variant != kVarHwcnVecNTap) || !(via || y16) || o.dma == 1) return;
+      c.a_mode = kAVecMB3;
+    }
     if (via) {
       auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
       c.via_hwcn = 1;
@@ -471,13 +491,13 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     if (o.dma == 1 && c.variant != kVarHwcnVecNTapDma) return;
     // runs spanning two tiles need the kernel's loop over pieces (only the
     // 32x32x2 fp32 kernel with the one-tap HWCN loader has it)
-    if (c.tail_wgs > 0 && c.sk_s == 0 && (c.acc64 || c.t.m16 || !tail_runs_multi(c.b_mode))) return;
+    if (c.tail_wgs > 0 && c.sk_s == 0 && (c.acc64 || c.t.m16 || !(c.b3 || tail_runs_multi(c.b_mode)))) return;
     // the persistent kernel is built for the batch-vector HWCN loaders only
-    if (c.persist && (c.acc64 || !persist_built(c.variant, c.t))) return;
+    if (c.persist && (c.acc64 || c.b3 || !persist_built(c.variant, c.t))) return;
     if (c.persist && sp == 0) {
       // the selector's persistent plans fill every slot the kernel's
       // occupancy allows, and only pay off with more tiles than that
-      const long long slots = (long long)kCUs * resident_wgs(c.t, false, c.variant);
+      const long long slots = (long long)kCUs * resident_wgs(c.t, kF32, c.variant);
       if (c.dp_tiles <= slots) return;
       c.grid = slots;
     }
@@ -503,12 +523,14 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     *err = "plan override: via=hwcn applies to NCHW calls of the fp32 kernel";
     return MG3M_ERR_PLAN;
   }
+  Family fam = acc64 ? kF64 : kF32;
   auto consider = [&](int ti, int sched, long long sp) {
-    if (o.via != 1) consider_one(ti, sched, sp, false);
-    if (via_ok && o.via != 0) consider_one(ti, sched, sp, true);
+    if (o.via != 1) consider_one(fam, ti, sched, sp, false);
+    if (via_ok && o.via != 0) consider_one(fam, ti, sched, sp, true);
   };
-  for (int ti = 0; ti < (acc64 ? kNumTiles64 : kNumTiles); ++ti) {
-    const TileDesc& td = tile_desc(acc64, ti);
+  auto consider_family = [&]() {
+  for (int ti = 0; ti < num_tiles(fam); ++ti) {
+    const TileDesc& td = tile_desc(fam, ti);
     if (o.mt && !(td.mt == o.mt && td.nt == o.nt)) continue;
     if (o.wm && !(td.wm == o.wm && td.wn == o.wn)) continue;
     // The selector takes a 16-row tile only where it saves padding, i.e. a
@@ -517,6 +539,9 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // A tile the cost model does not yet rank correctly is left to overrides
     // that name its shape and its waves.
     if (td.forced_only && !(o.mt && o.wm)) continue;
+    // 1x1 layers take the bf16 part products on the 64x64 tile only (their
+    // time is mostly their bytes and launches; see the tile menu)
+    if (fam == kB3 && !o.mt && s.R * s.S == 1 && !(td.mt == 64 && td.nt == 64 && td.kt == 32)) continue;
     // a forced tile without a depth means the default depth of 16
     if ((o.kt || o.mt) && td.kt != (o.kt ? o.kt : 16)) continue;
     if (o.split) {
@@ -534,10 +559,16 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
         consider(ti, kSplitTail, sp);
       }
       // stream-K over the left-over tiles with one to all resident work-groups per CU
-      for (int j = 1, occ = resident_wgs(td, acc64); j <= occ; ++j) consider(ti, kStreamK, (long long)j * kCUs);
+      for (int j = 1, occ = resident_wgs(td, fam); j <= occ; ++j) consider(ti, kStreamK, (long long)j * kCUs);
       // every tile whole, persistent work-groups filling the chip
-      if (!acc64) consider(ti, kPersistent, 0);
+      if (fam == kF32) consider(ti, kPersistent, 0);
     }
+  }
+  };
+  consider_family();
+  if (!acc64) {
+    fam = kB3;
+    consider_family();
   }
   if (best < 0 && least_over_cap != SIZE_MAX) {
     *err = "every applicable plan needs more workspace than the " + std::to_string(ws_cap) +
@@ -566,7 +597,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
 }
 
 std::string plan_to_string(const ConvShape& s, const Plan& p) {
-  static const char* an[] = {"vec_m", "vec_k", "scalar"};
+  static const char* an[] = {"vec_m", "vec_k", "scalar", "vec_m_b3"};
   static const char* bn[] = {"vec_n", "vec_c", "scalar", "vec_n_tap", "vec_w", "vec_w_tap", "vec_n_tap_dma"};
   static const char* en[] = {"elem", "vec_m"};
   char buf[512];

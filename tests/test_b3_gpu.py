@@ -1,0 +1,165 @@
+"""GPU parity of the kernel that takes fp32 products as bf16 part products
+(plan strings with a=vec_m_b3): every tile through whole, split and stream-K
+schedules on ragged shapes (rows and columns that do not fill a tile, odd
+stage counts, padding, strides), bit-exact on small-integer data; its error
+against the fp64 oracle no larger than the fp32-MFMA kernel's; operands whose
+24 significand bits are all in use; and the range check: infinities, NaNs,
+overflow and values near the bottom of the exponent range come out as the
+fp32-MFMA kernel (dma=1) gives them."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2307_04941_amd import mg3m
+from tests.gpu_util import assert_parity, make, run_gpu, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+TILES = ["tile=128x128,waves=1x4,kt=32", "tile=128x256,waves=1x8,kt=32", "tile=64x256,waves=1x8,kt=64",
+         "tile=64x128,waves=1x4,kt=64", "tile=64x128,waves=1x4,kt=32", "tile=64x64,waves=1x4,kt=32",
+         "tile=64x64,waves=1x4,kt=64", "tile=32x128,waves=1x4,kt=32"]
+
+# (N, C, H, W, K, R, S, stride, pad): one stage; an odd count; 3x3 with ragged
+# rows and columns; stride 2 with an even window
+SHAPES = [(4, 64, 3, 5, 20, 1, 1, 1, 0), (8, 192, 7, 5, 132, 1, 1, 1, 0), (4, 64, 13, 11, 68, 3, 3, 1, 1),
+          (12, 128, 9, 10, 36, 2, 3, 2, 1)]
+
+
+def _is_b3(shape, plan):
+    return "a=vec_m_b3" in mg3m.conv2d_fwd_f32_plan_string(*shape, "HWCN", plan)
+
+
+@pytest.mark.parametrize("tile", TILES)
+def test_every_b3_tile_exact(tile):
+    for si, shape in enumerate(SHAPES):
+        x, w, st, pd = make(shape, 3300 + si, "HWCN", dist="int")
+        acc, _ = oracle.conv2d(x, w, st, pd, "HWCN")
+        for sched in ("split=1", "split=2", "split=5", "sk=7"):
+            plan = f"{tile},{sched}"
+            try:
+                assert _is_b3(shape, plan), plan
+            except mg3m.Mg3mError:
+                assert sched == "sk=7", plan         # fewer k-tiles than work-groups, or more tiles
+                continue
+            say(f"b3 {plan} {shape}")
+            y = run_gpu(x, w, st, pd, "HWCN", plan=plan)
+            assert np.array_equal(y, acc.astype(np.float32)), f"{shape} {plan}: not bit-exact"
+
+
+@pytest.mark.parametrize("Kg", [(64, 1), (64, 3), (512, 3)])
+def test_b3_error_no_larger_than_fp32_mfma(Kg):
+    """Root-mean-square error against fp64 on He-normal filters and clamped
+    activations; the fp32-MFMA kernel on the same data is the bound."""
+    C, R = Kg
+    shape = (8, C, 9, 9, 64, R, R, 1, R // 2)
+    x, w, st, pd = make(shape, 3400 + C + R, "HWCN")
+    x = np.maximum(x, 0)
+    acc, mag = oracle.conv2d(x, w, st, pd, "HWCN")
+    err = []
+    for plan in ("tile=64x128,waves=1x4,kt=32", "dma=1"):
+        y = run_gpu(x, w, st, pd, "HWCN", plan=plan)
+        assert_parity(y, acc, mag, f"{shape} {plan}")
+        err.append(float(np.sqrt(np.mean((y.astype(np.float64) - acc) ** 2) / np.mean(acc ** 2))))
+    say(f"C={C} R={R}: rms error b3 {err[0]:.3g}, fp32 MFMA {err[1]:.3g}")
+    assert err[0] <= err[1], err
+
+
+def test_b3_keeps_every_bit():
+    """A filter that picks one element: y is a shifted copy of x, bit for bit,
+    whatever the 24 bits; and the same with the roles of x and w exchanged."""
+    rng = np.random.Generator(np.random.PCG64(3500))
+    N, C, H, W, K = 4, 64, 6, 7, 64
+    bits = rng.integers(0, 2**23, (H, W, C, N), dtype=np.uint32) | (rng.integers(64, 190, (H, W, C, N), dtype=np.uint32) << 23)
+    x = (bits | (rng.integers(0, 2, bits.shape, dtype=np.uint32) << 31)).view(np.float32)
+    w = np.zeros((3, 3, C, K), np.float32)
+    for k in range(K):
+        w[k % 3, (k // 3) % 3, (5 * k) % C, k] = 1.0
+    plan = "tile=64x128,waves=1x4,kt=64"
+    y = run_gpu(x, w, 1, 1, "HWCN", plan=plan)
+    xp = np.pad(x, ((1, 1), (1, 1), (0, 0), (0, 0)))
+    for k in range(K):
+        assert np.array_equal(y[:, :, k], xp[k % 3:k % 3 + H, (k // 3) % 3:(k // 3) % 3 + W, (5 * k) % C]), k
+    wv = x[0, 0].reshape(1, 1, C, N)                   # 1x1 filter of arbitrary bits, one-hot pixels
+    e = np.zeros((8, 8, C, 4), np.float32)
+    for p in range(64):
+        e[p // 8, p % 8, p, :] = 1.0
+    y = run_gpu(e, np.ascontiguousarray(wv), 1, 0, "HWCN", plan="tile=64x64,waves=1x4,kt=32")
+    assert np.array_equal(y[:, :, :, 0].reshape(64, N), wv[0, 0])
+
+
+def _special(kind, x, w):
+    x, w = x.copy(), w.copy()
+    if kind == "inf":
+        x[3, 2, 5, 1] = np.inf
+        x[0, 0, 0, 0] = -np.inf
+    elif kind == "nan":
+        x[3, 2, 5, 1] = np.nan
+    elif kind == "inf_filter":
+        w[1, 1, 7, 3] = np.inf
+    elif kind == "near_max":                           # rounds to infinity in bf16, not in fp32
+        x[3, 2, 5, 1] = np.float32(3.4e38)
+        w[:] *= np.float32(1e-3)
+    elif kind == "overflow":
+        x *= np.float32(1e30)
+        w *= np.float32(1e20)
+    elif kind == "tiny":                               # parts would fall below the denormal range
+        x *= np.float32(2.0**-116)
+    elif kind == "tiny_sums":
+        x *= np.float32(2.0**-70)
+        w *= np.float32(2.0**-70)
+    return x, w
+
+
+@pytest.mark.parametrize("kind", ["inf", "nan", "inf_filter", "near_max", "overflow", "tiny", "tiny_sums"])
+@pytest.mark.parametrize("plan", ["tile=64x128,waves=1x4,kt=64,split=1", "tile=128x128,waves=1x4,kt=32,sk=3",
+                                  "tile=64x64,waves=1x4,kt=32,split=2"])
+def test_b3_range_check(kind, plan):
+    import torch
+    shape = (4, 64, 6, 5, 68, 3, 3, 1, 1)
+    assert _is_b3(shape, plan)
+    x, w, st, pd = make(shape, 3600, "HWCN")
+    x, w = _special(kind, x, w)
+    y = run_gpu(x, w, st, pd, "HWCN", plan=plan)
+    ref = run_gpu(x, w, st, pd, "HWCN", plan="dma=1")
+    say(f"{kind} {plan}: {int((~np.isfinite(ref)).sum())} non-finite outputs, {int((ref == 0).sum())} zeros")
+    # a sum that overflows does so depending on its order: infinite or NaN in both
+    if kind == "overflow":
+        assert np.array_equal(np.isfinite(y), np.isfinite(ref))
+    else:
+        assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isposinf(y), np.isposinf(ref))
+        assert np.array_equal(np.isneginf(y), np.isneginf(ref))
+    fin = np.isfinite(y) & np.isfinite(ref)
+    with np.errstate(over="ignore", invalid="ignore"):
+        xs, ws = np.where(np.isfinite(x), x, 0).astype(np.float64), np.where(np.isfinite(w), w, 0).astype(np.float64)
+    mag = _magnitude(np.abs(xs), np.abs(ws))
+    # two fp32 sums of 576 products: 1e-5 of the magnitudes, or the fp32 denormal step
+    assert np.all(np.abs(y.astype(np.float64) - ref)[fin] <= 1e-5 * mag[fin] + 600 * 2.0**-149)
+
+
+def _magnitude(x, w):
+    xp = np.pad(x, ((1, 1), (1, 1), (0, 0), (0, 0)))
+    H, W = x.shape[:2]
+    out = np.zeros((H, W, w.shape[3], x.shape[3]))
+    for r in range(3):
+        for s in range(3):
+            out += np.einsum("hwcn,ck->hwkn", xp[r:r + H, s:s + W], w[r, s])
+    return out
+
+
+def test_b3_fused_in_place_with_infinity():
+    """relu(conv + add) with add == y: the range check recomputes a tile before
+    anything of it is stored, so add is read once."""
+    import torch
+    shape = (4, 64, 6, 5, 68, 3, 3, 1, 1)
+    x, w, st, pd = make(shape, 3700, "HWCN")
+    x[2, 2, 3, 1] = np.inf
+    add = np.random.Generator(np.random.PCG64(3701)).standard_normal((6, 5, 68, 4)).astype(np.float32)
+    out = []
+    for plan in ("tile=64x128,waves=1x4,kt=32,split=1", "tile=64x64,waves=1x1,kt=16,split=1"):
+        y = to_dev(add)
+        mg3m.conv2d_fwd_f32_fused(to_dev(x), to_dev(w), y, y, 1, 4, 64, 6, 5, 68, 3, 3, 1, 1, 1, 1, "HWCN", None, 0, plan)
+        torch.cuda.synchronize()
+        out.append(y.cpu().numpy())
+    assert np.array_equal(np.isnan(out[0]), np.isnan(out[1])) and np.array_equal(np.isinf(out[0]), np.isinf(out[1]))
+    fin = np.isfinite(out[1])
+    assert np.isinf(out[1]).any() and np.all(np.abs(out[0] - out[1])[fin] <= 1e-4)

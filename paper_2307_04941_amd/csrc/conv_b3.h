@@ -114,6 +114,61 @@ struct B3Cfg {
   static_assert(LDS_CHUNKS * 16 == lds_bytes_for_b3(TileDesc{MT, NT, KT, 1, WN, 0, 0.0}), "LDS size model");
 };
 
+// How the operands are addressed (kernel variants; plan.cpp chooses).
+//  kB3Slab   C % KT == 0: a stage is one filter tap over KT channels (taps
+//            inside channel slabs, as the fp32 one-tap kernels), its tap in
+//            scalar registers; HWCN, N % 4 == 0: a lane's TN columns are one load.
+//  kB3SlabW  the same stages in NCHW on the [R][S][C][K] filter copy: 16 lanes
+//            along the output pixels, a load per column.
+//  kB3Group  C % 8 == 0: the reduction runs tap by tap over groups of eight
+//            channels, four groups to a k-step, so each lane group has a tap and
+//            channels of its own.  HWCN, N % 4 == 0, columns as kB3Slab.
+//  kB3GroupN the same for any N: a load per column.
+//  kB3GroupC the same for N == 1: a group's channels are contiguous, two 16-byte
+//            loads per column.
+//  kB3Row    any C: the reduction runs tap by tap over single channels, each row
+//            of the stage with a tap and channel of its own, stepped one row
+//            after another as they are loaded.  HWCN, N % 4 == 0, columns as
+//            kB3Slab.
+//  kB3RowN   the same for any N: a load per column.
+// (enum B3Load, mg3m_internal.h)
+constexpr bool b3_vec(int ld) { return ld == kB3Slab || ld == kB3Group || ld == kB3Row; }   // a lane's columns are consecutive
+constexpr bool b3_rows(int ld) { return ld >= kB3Row; }
+
+// Position of a lane (or thread) in the reduction of the group and row
+// variants: tap (r, s) and channel group (row variants: channel) g of the G
+// per tap; moved by `step` at a time, given in the mixed radix of (R, S, G).
+struct GroupStep {
+  int dr, ds, dg, G;
+  __device__ void init(const KArgs& a, int G_, int step) {
+    G = G_;
+    ds = step / G;
+    dg = step - ds * G;
+    dr = ds / a.S;
+    ds -= dr * a.S;
+  }
+};
+struct GroupPos {
+  int r, s, g;
+  __device__ void init(const KArgs& a, int G, int group) {
+    const int tap = group / G;
+    g = group - tap * G;
+    r = tap / a.S;
+    s = tap - r * a.S;
+  }
+  __device__ void advance(const KArgs& a, const GroupStep& st) {
+    g += st.dg;
+    s += st.ds;
+    r += st.dr;
+    if (g >= st.G) { g -= st.G; ++s; }
+    if (s >= a.S) { s -= a.S; ++r; }
+  }
+  __device__ void next(const KArgs& a, int G) {
+    if (++g == G) { g = 0; ++s; }
+    if (s == a.S) { s = 0; ++r; }
+  }
+};
+
 // Stage order: taps inside channel slabs, as the fp32 one-tap kernels.
 struct TapPos {
   int r, s, c0;
@@ -141,13 +196,16 @@ struct TapPos {
 constexpr unsigned kB3TinyBits = 0x14800000u;
 
 // One tile's product over the k-tiles [kt0, kt0 + nk), handed to store(acc,
-// m0, column in the tile, column n, g4, whether n exists): acc[i][j][e] is row 16*i +
-// 4*g4 + e, column n + j.
-template <int MT, int NT, int KT, int WN, class Store>
+// m0, n0, wave's first column in the tile, g4, q): acc[i][j][e] is row 16*i +
+// 4*g4 + e, and column TN*q + j of the wave (b3_vec) or 16*j + q.
+template <int LD, int MT, int NT, int KT, int WN, class Store>
 __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int t, int tile, int kt0, int nk,
                                                 Store&& store) {
   using C = B3Cfg<MT, NT, KT, WN>;
   constexpr int TM = C::TM, TN = C::TN, KS = C::KS;
+  constexpr bool kGroups = b3_groups(LD), kRows = b3_rows(LD), kVec = b3_vec(LD);   // kGroups: kRows too
+  constexpr int NB = kVec ? 1 : TN;      // patch addresses per lane
+  static_assert(!kGroups || (KS == 1 && C::UA == 1), "one group of eight rows, or a part of it, per thread");
   const int m0 = (tile % a.tiles_m) * MT, n0 = (tile / a.tiles_m) * NT;
   const int wn = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   const int g4 = lane >> 4, q = lane & 15;
@@ -156,18 +214,31 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
 
   // filter: thread t takes column m0 + t % MT, AR rows of the stage from AR*(t / MT)
   const int am = m0 + t % MT, ak = t / MT * C::AR;
-  const unsigned avoff = (am < a.Mg) ? 4u * (unsigned)(am + ak * a.K) : kOOB;
+  const bool am_ok = am < a.Mg;
   unsigned* const aslot = reinterpret_cast<unsigned*>(lds) + 4 * ((ak >> 3) * MT + t % MT) + (ak & 7) / 2;
-  // patches: this lane's TN consecutive columns, all of one pixel (N % 4 == 0),
-  // and rows 8*g4 .. 8*g4+7 of each 32: its part of the MFMA's operand, so
-  // the patches never go through LDS (no other wave of the group needs them)
-  const int col = wn * C::WTN + q * TN, n = n0 + col;
-  const bool col_ok = n < a.Ng;
-  const int pix = n / a.N, b = n - pix * a.N, ho = pix / a.Wo;
-  const int ih0 = ho * a.sh - a.ph, iw0 = (pix - ho * a.Wo) * a.sw - a.pw;
-  const int bbase4 = 4 * (((ih0 * a.W + iw0) * a.C + 8 * g4) * a.N + b);
-  const unsigned N4 = 4u * (unsigned)a.N, K4 = 4u * (unsigned)a.K;
-  const int tap_w4 = 4 * a.C * a.N, tap_h4 = a.W * tap_w4;
+  // patches: this lane's TN columns, and rows 8*g4 .. 8*g4+7 of each 32: its
+  // part of the MFMA's operand, so the patches never go through LDS (no other
+  // wave of the group needs them)
+  int ih0[NB], iw0[NB];
+  unsigned bbase[NB];                // bytes to the column's pixel at tap (0, 0); wraps below zero at the border
+  bool col_ok[NB];
+  const unsigned C4 = 4u * (unsigned)(LD == kB3SlabW ? a.H * a.W : a.N);   // bytes between channels
+  const unsigned tap_w4 = LD == kB3SlabW ? 4u : 4u * (unsigned)(a.C * a.N), tap_h4 = (unsigned)a.W * tap_w4;
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int n = n0 + wn * C::WTN + (kVec ? q * TN : 16 * j + q);
+    col_ok[j] = n < a.Ng;
+    int pix, b;
+    if constexpr (LD == kB3SlabW) { const int hw = a.Ho * a.Wo; b = n / hw; pix = n - b * hw; }
+    else if constexpr (LD == kB3GroupC) { b = 0; pix = n; }
+    else { pix = n / a.N; b = n - pix * a.N; }
+    const int ho = pix / a.Wo;
+    ih0[j] = ho * a.sh - a.ph;
+    iw0[j] = (pix - ho * a.Wo) * a.sw - a.pw;
+    if constexpr (LD == kB3SlabW) bbase[j] = 4u * (unsigned)(((b * a.C + 8 * g4) * a.H + ih0[j]) * a.W + iw0[j]);
+    else bbase[j] = 4u * (unsigned)(((ih0[j] * a.W + iw0[j]) * a.C + (kGroups ? 0 : 8 * g4)) * a.N + b);
+  }
+  const unsigned K4 = 4u * (unsigned)a.K;
 
   float fa[C::UA][C::AR];            // loaded, not yet split
   float fb[8][TN];
@@ -177,20 +248,113 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
   // Where the next loads go.  Patches are loaded two k-steps ahead, the filter
   // two stages ahead.
   TapPos pa, pb;
-  unsigned bv, as, bs;
-  auto place_a = [&]() { as = (unsigned)((pa.r * a.S + pa.s) * a.C + pa.c0) * K4; };
+  GroupPos ga, gb;
+  GroupStep gst;
+  unsigned av, bv[NB], as = 0, bs = 0;
+  int arow = 0;
+  unsigned brow = 0;                 // row variants: the thread's first filter row, and the bytes to the lane's row
+  bool blive = true;
+  const int G = kRows ? a.C : a.C >> 3;
+  auto start_a = [&](int kt) {
+    if constexpr (kRows) arow = kt * KT + ak;
+    else if constexpr (kGroups) ga.init(a, G, kt * (KT / 8) + (ak >> 3));
+    else pa.init(a, kt, KT);
+  };
+  auto start_b = [&](int kt) {
+    if constexpr (kGroups) gb.init(a, G, kRows ? kt * KT + 8 * g4 : kt * (KT / 8) + g4);
+    else pb.init(a, kt, KT);
+  };
+  auto advance_a = [&](bool more) {
+    if constexpr (kRows) arow += KT;
+    else if constexpr (kGroups) ga.advance(a, gst);
+    else pa.advance(a, KT, more);
+  };
+  auto advance_b = [&](bool more) {
+    if constexpr (kGroups) gb.advance(a, gst);
+    else pb.advance(a, KT, more);
+  };
+  auto place_a = [&]() {
+    if constexpr (kRows) {
+      av = 4u * (unsigned)(arow * a.K + am);
+    } else if constexpr (kGroups) {
+      const int c = 8 * ga.g + (ak & 7);
+      const bool ok = am_ok & (ga.r < a.R);
+      const unsigned at = 4u * (unsigned)(((ga.r * a.S + ga.s) * a.C + c) * a.K + am);
+      av = ok ? at : kOOB;
+    } else {
+      av = am_ok ? 4u * (unsigned)(am + ak * a.K) : kOOB;
+      as = (unsigned)((pa.r * a.S + pa.s) * a.C + pa.c0) * K4;
+    }
+  };
   auto place_b = [&](bool live, int ks) {
-    const bool ok = live & col_ok & ((unsigned)(ih0 + pb.r) < (unsigned)a.H) & ((unsigned)(iw0 + pb.s) < (unsigned)a.W);
-    const unsigned at = (unsigned)(bbase4 + pb.r * tap_h4 + pb.s * tap_w4);
-    bv = ok ? at : kOOB;
-    bs = (unsigned)(pb.c0 + 32 * ks) * N4;
+    if constexpr (kRows) {
+      brow = (unsigned)gb.r * tap_h4 + (unsigned)gb.s * tap_w4 + (unsigned)gb.g * C4;
+      blive = live;
+      return;
+    }
+    const int r = kGroups ? gb.r : pb.r, s = kGroups ? gb.s : pb.s;
+    const unsigned off = (unsigned)r * tap_h4 + (unsigned)s * tap_w4 + (kGroups ? 8u * (unsigned)gb.g * C4 : 0u);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const bool ok = live & col_ok[j] & ((unsigned)(ih0[j] + r) < (unsigned)a.H) &
+                      ((unsigned)(iw0[j] + s) < (unsigned)a.W) & (!kGroups || r < a.R);
+      const unsigned at = bbase[j] + off;
+      bv[j] = ok ? at : kOOB;
+    }
+    if constexpr (!kGroups) bs = (unsigned)(pb.c0 + 32 * ks) * C4;
   };
   auto load_a = [&](int u, int i) {
     float v[1];
-    bload_w<1>(wr, avoff, as + (unsigned)(u * (C::T / MT) * C::AR + i) * K4, v);
+    if constexpr (kRows) bload_w<1>(wr, am_ok & (arow + i < a.Kg) ? av : kOOB, (unsigned)i * K4, v);
+    else if constexpr (kGroups) bload_w<1>(wr, av, (unsigned)i * K4, v);
+    else bload_w<1>(wr, av, as + (unsigned)(u * (C::T / MT) * C::AR + i) * K4, v);
     fa[u][i] = v[0];
   };
-  auto load_b = [&](int i) { bload_w<TN>(xr, bv, bs + (unsigned)i * N4, fb[i]); };
+  auto load_b = [&](int i) {
+    const unsigned rowC4 = C4 * (unsigned)i;
+    if constexpr (kRows) {
+      // the row's address, then on to the next row: channels and the taps of
+      // one filter row follow each other in x, the next filter row is W - S
+      // pixels on
+      const bool live = blive & (gb.r < a.R);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const bool ok = live & col_ok[j] & ((unsigned)(ih0[j] + gb.r) < (unsigned)a.H) &
+                        ((unsigned)(iw0[j] + gb.s) < (unsigned)a.W);
+        const unsigned at = bbase[j] + brow;
+        if constexpr (kVec) {
+          bload_w<TN>(xr, ok ? at : kOOB, 0u, fb[i]);
+        } else {
+          float v[1];
+          bload_w<1>(xr, ok ? at : kOOB, 0u, v);
+          fb[i][j] = v[0];
+        }
+      }
+      const int r0 = gb.r;
+      gb.next(a, G);
+      brow += C4 + (gb.r != r0 ? tap_h4 - (unsigned)a.S * tap_w4 : 0u);
+    } else if constexpr (LD == kB3GroupC) {
+      // rows i .. i+3 at once
+      if (i % 4 == 0) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          float v[4];
+          bload_w<4>(xr, bv[j], 4u * (unsigned)i, v);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) fb[i + e][j] = v[e];
+        }
+      }
+    } else if constexpr (kVec) {
+      bload_w<TN>(xr, bv[0], bs + rowC4, fb[i]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        float v[1];
+        bload_w<1>(xr, bv[j], bs + rowC4, v);
+        fb[i][j] = v[0];
+      }
+    }
+  };
 
   // The split work in pieces of two rows of one column.
   constexpr int ITB = 4 * TN;                          // per k-step
@@ -223,9 +387,13 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
     }
   };
   auto reload_b = [&](int it) {
-    if (it % TN == TN - 1) {
-      load_b(2 * (it / TN));
-      load_b(2 * (it / TN) + 1);
+    if (it % TN != TN - 1) return;
+    const int p = it / TN;
+    if constexpr (LD == kB3GroupC) {
+      if (p % 2 == 1) load_b(2 * p - 2);
+    } else {
+      load_b(2 * p);
+      load_b(2 * p + 1);
     }
   };
   auto reload_a = [&](int it) {
@@ -292,8 +460,9 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
 
   // Stages go in pairs, one per LDS buffer, KS k-steps each.  Past the last
   // one the patch columns are out of range and the filter address stays.
-  pa.init(a, kt0, KT);
-  pb = pa;
+  if constexpr (kGroups) gst.init(a, G, kRows ? KT - 8 : KT / 8);   // rows: eight are stepped by their loads
+  start_a(kt0);
+  start_b(kt0);
   place_a();
 #pragma unroll
   for (int it = 0; it < ITA; ++it) reload_a(it);
@@ -304,11 +473,11 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
   for (int it = 0; it < ITA; ++it) split_a(it, 0);
 #pragma unroll
   for (int it = 0; it < ITB; ++it) split_b(it, 0);
-  pa.advance(a, KT, nk > 1);
+  advance_a(nk > 1);
   place_a();
 #pragma unroll
   for (int it = 0; it < ITA; ++it) reload_a(it);
-  if constexpr (KS == 1) pb = pa;
+  if constexpr (KS == 1) advance_b(nk > 1);
   place_b(KS > 1 || nk > 1, KS > 1 ? 1 : 0);
 #pragma unroll
   for (int it = 0; it < ITB; ++it) reload_b(it);
@@ -316,12 +485,12 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
   auto stage = [&](int it, auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
     poison(buf ^ 1);
-    pa.advance(a, KT, it + 2 < nk);
+    advance_a(it + 2 < nk);
     place_a();
     static_for<KS>([&](auto ks_c) {
       // k-step ks of stage it loads the patches two k-steps on
       constexpr int ks = decltype(ks_c)::value, step = ks + 2;
-      if constexpr (step % KS == 0) pb.advance(a, KT, it + step / KS < nk);
+      if constexpr (step % KS == 0) advance_b(it + step / KS < nk);
       place_b(it + step / KS < nk, step % KS);
       __builtin_amdgcn_sched_barrier(0);
       kstep(buf_c, ks_c);
@@ -351,117 +520,139 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
     // memory: step k of 32 rows takes rows 8*g + k of each lane group g, the
     // rows that the lanes' patches hold.
     clear();
-    pb.init(a, kt0, KT);
-    const unsigned fvoff = 4u * (unsigned)(8 * g4 * a.K + m0 + q);
+    start_b(kt0);
     for (int it = 0; it < nk; ++it) {
 #pragma unroll 1
       for (int ks = 0; ks < KS; ++ks) {
         place_b(true, ks);
 #pragma unroll
         for (int k = 0; k < ITB; ++k) reload_b(k);
-        const unsigned fs = (unsigned)((pb.r * a.S + pb.s) * a.C + pb.c0 + 32 * ks) * K4;
+        // the lane group's first filter row
+        const int row = kRows ? (kt0 + it) * KT + 8 * g4
+                        : kGroups ? (gb.r * a.S + gb.s) * a.C + 8 * gb.g
+                                : (pb.r * a.S + pb.s) * a.C + pb.c0 + 32 * ks + 8 * g4;
+        const unsigned fv = 4u * (unsigned)(row * a.K + m0 + q);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
+          const bool row_ok = kRows ? row + k < a.Kg : !kGroups || gb.r < a.R;
 #pragma unroll
           for (int i = 0; i < TM; ++i) {
             float f[1];
-            bload_w<1>(wr, m0 + i * 16 + q < a.Mg ? fvoff + 64u * i : kOOB, fs + (unsigned)k * K4, f);
+            bload_w<1>(wr, row_ok & (m0 + i * 16 + q < a.Mg) ? fv + 64u * i : kOOB, (unsigned)k * K4, f);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
               acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[0], fb[k][j], acc[i][j], 0, 0, 0);
           }
         }
       }
-      pb.advance(a, KT, it + 1 < nk);
+      advance_b(it + 1 < nk);
     }
   }
-  store(acc, m0, col, n, g4, col_ok);
+  store(acc, m0, n0, wn * C::WTN, g4, q);
 }
 
 // Schedule and tails as conv_igemm_f32: whole tiles grouped per XCD, then the
 // tail work-groups, whose pieces (split, or stream-K runs of up to two) leave
 // tile-local partials for the tail reduction.
-template <int MT, int NT, int KT, int WN, bool FUSE>
+template <int LD, int MT, int NT, int KT, int WN, bool FUSE>
 __global__ __launch_bounds__(WN * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void conv_igemm_b3(KArgs a) {
   using C = B3Cfg<MT, NT, KT, WN>;
   constexpr int TM = C::TM, TN = C::TN;
+  constexpr bool kVec = b3_vec(LD);
+  constexpr int NS = kVec ? 1 : TN, SW = kVec ? TN : 1;      // stores per row, and their width
   __shared__ __attribute__((aligned(16))) u32x4 lds[C::LDS_CHUNKS];
 
-  if ((int)blockIdx.x >= a.dp_tiles) {
-    const int w = tail_wg(a, blockIdx.x - a.dp_tiles);
-    TailRun run = tail_run(a, w);
-    for (;;) {
-      int rel, kt0, nk;
+  // One call of the product for whole tiles and pieces: a second copy of its
+  // code would cost registers, scalar ones above all.
+  const bool whole = (int)blockIdx.x < a.dp_tiles;
+  const int w = whole ? 0 : tail_wg(a, blockIdx.x - a.dp_tiles);
+  TailRun run = whole ? TailRun{0, 0} : tail_run(a, w);
+  for (;;) {
+    int rel = 0, kt0 = 0, nk = a.k_tiles, tile = xcd_group(blockIdx.x, a.dp_tiles);
+    if (!whole) {
       tail_piece(a, run, &rel, &kt0, &nk);
-      int t = threadIdx.x;
-      asm volatile("" : "+v"(t));
-      const __amdgpu_buffer_rsrc_t pr = make_rsrc(a.ws + tail_slot(w, rel) * (MT * NT), MT * NT * 4);
-      tile_product_b3<MT, NT, KT, WN>(
-          a, lds, t, a.dp_tiles + rel, kt0, nk, [&](f32x4 (&acc)[TM][TN], int, int col, int, int g4, bool) {
-            const unsigned lane_b = 4u * (unsigned)(4 * g4 * NT + col);
+      tile = a.dp_tiles + rel;
+    }
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    tile_product_b3<LD, MT, NT, KT, WN>(
+        a, lds, t, tile, kt0, nk, [&](f32x4 (&acc)[TM][TN], int m0, int n0, int wcol, int g4, int q) {
+          if (!whole) {
+            const __amdgpu_buffer_rsrc_t pr = make_rsrc(a.ws + tail_slot(w, rel) * (MT * NT), MT * NT * 4);
+            const unsigned lane_b = 4u * (unsigned)(4 * g4 * NT + wcol + (kVec ? q * TN : q));
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int u = 0; u < NS; ++u) {
+                  float v[SW];
+#pragma unroll
+                  for (int j = 0; j < SW; ++j) v[j] = acc[i][u + j][e];
+                  bstore_w<SW>(pr, lane_b, 4u * ((i * 16 + e) * NT + 16 * u), v);
+                }
+            return;
+          }
+          const __amdgpu_buffer_rsrc_t yr = make_rsrc(a.y, a.y_bytes);
+          const bool has_add = FUSE && a.add != nullptr;
+          const __amdgpu_buffer_rsrc_t ar = make_rsrc(has_add ? a.add : a.y, a.y_bytes);
+          unsigned rs4 = 4u * (unsigned)a.mstride;
+          asm volatile("" : "+s"(rs4));
+          const int row_l = m0 + 4 * g4, rows_left = a.Mg - row_l;
+#pragma unroll
+          for (int u = 0; u < NS; ++u) {
+            const int n = n0 + wcol + (kVec ? q * TN : 16 * u + q);
+            const bool col_ok = n < a.Ng;
+            const unsigned voff =
+                4u * (unsigned)(out_colbase<LD == kB3SlabW ? kNCHW : kHWCN>(a, n) + row_l * a.mstride);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                float v[TN];
+                const bool ok = col_ok & (i * 16 + e < rows_left);
+                const unsigned off = ok ? voff + (unsigned)(i * 16 + e) * rs4 : kOOB;
+                float v[SW];
 #pragma unroll
-                for (int j = 0; j < TN; ++j) v[j] = acc[i][j][e];
-                bstore_w<TN>(pr, lane_b, 4u * ((i * 16 + e) * NT), v);
+                for (int j = 0; j < SW; ++j) v[j] = acc[i][u + j][e];
+                if constexpr (FUSE) {
+                  float d[SW];
+                  if (has_add) {
+                    bload_w<SW>(ar, off, 0u, d);
+#pragma unroll
+                    for (int j = 0; j < SW; ++j) v[j] += d[j];
+                  }
+                  if (a.relu != 0) {
+#pragma unroll
+                    for (int j = 0; j < SW; ++j)
+                      if (v[j] < 0.f) v[j] = 0.f;     // NaN kept
+                  }
+                }
+                bstore_w<SW>(yr, off, 0u, v);
               }
-          });
-      run.it += nk;
-      if (run.it >= run.end) return;
-      __syncthreads();   // the next piece restages the LDS buffers
-    }
-  }
-  const int tile = xcd_group(blockIdx.x, a.dp_tiles);
-  tile_product_b3<MT, NT, KT, WN>(
-      a, lds, threadIdx.x, tile, 0, a.k_tiles, [&](f32x4 (&acc)[TM][TN], int m0, int, int n, int g4, bool col_ok) {
-        const __amdgpu_buffer_rsrc_t yr = make_rsrc(a.y, a.y_bytes);
-        const bool has_add = FUSE && a.add != nullptr;
-        const __amdgpu_buffer_rsrc_t ar = make_rsrc(has_add ? a.add : a.y, a.y_bytes);
-        unsigned rs4 = 4u * (unsigned)a.mstride;
-        asm volatile("" : "+s"(rs4));
-        const int row_l = m0 + 4 * g4, rows_left = a.Mg - row_l;
-        const unsigned voff = 4u * (unsigned)(out_colbase<kHWCN>(a, n) + row_l * a.mstride);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bool ok = col_ok & (i * 16 + e < rows_left);
-            const unsigned off = ok ? voff + (unsigned)(i * 16 + e) * rs4 : kOOB;
-            float v[TN];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) v[j] = acc[i][j][e];
-            if constexpr (FUSE) {
-              float d[TN];
-              if (has_add) {
-                bload_w<TN>(ar, off, 0u, d);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) v[j] += d[j];
-              }
-              if (a.relu != 0) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                  if (v[j] < 0.f) v[j] = 0.f;     // NaN kept
-              }
-            }
-            bstore_w<TN>(yr, off, 0u, v);
           }
-      });
+        });
+    run.it += nk;
+    if (whole || run.it >= run.end) return;
+    __syncthreads();   // the next piece restages the LDS buffers
+  }
 }
 
-template <bool FUSE, int TI>
+template <int LD, bool FUSE, int TI>
 constexpr KernelFn b3_kernel_at() {
   constexpr TileDesc d = kTilesB3[TI];
-  return &conv_igemm_b3<d.mt, d.nt, d.kt, d.wn, FUSE>;
+  if constexpr (b3_built(LD, TI)) return &conv_igemm_b3<LD, d.mt, d.nt, d.kt, d.wn, FUSE>;
+  else return nullptr;
 }
-template <bool FUSE, int... TI>
+template <int LD, bool FUSE, int... TI>
 KernelFn pick_b3(int tile, std::integer_sequence<int, TI...>) {
   KernelFn fn = nullptr;
-  ((fn = (tile == TI ? b3_kernel_at<FUSE, TI>() : fn)), ...);
+  ((fn = (tile == TI ? b3_kernel_at<LD, FUSE, TI>() : fn)), ...);
   return fn;
+}
+template <int LD, bool FUSE>
+KernelFn b3_kernel_for_tile(int tile) {
+  return pick_b3<LD, FUSE>(tile, std::make_integer_sequence<int, kNumTilesB3>{});
 }
 
 }  // namespace mg3m

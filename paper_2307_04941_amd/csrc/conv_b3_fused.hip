@@ -1,11 +1,15 @@
-// Instantiations of the kernel of bf16 part products with the fused output
-// stage (add, ReLU), one per tile shape.
+// Instantiations of the kernel that takes fp32 products as bf16 part products, with the fused output stage:
+// the forms whose stages are one filter tap, HWCN and NCHW.
 #include "conv_b3.h"
 
 namespace mg3m {
 
-KernelFn conv_kernel_b3_fused(int tile) {
-  return pick_b3<true>(tile, std::make_integer_sequence<int, kNumTilesB3>{});
+KernelFn conv_kernel_b3_fused(int load, int tile) {
+  switch (load) {
+    case kB3Slab: return b3_kernel_for_tile<kB3Slab, true>(tile);
+    case kB3SlabW: return b3_kernel_for_tile<kB3SlabW, true>(tile);
+    default: return conv_kernel_b3_any_fused(load, tile);
+  }
 }
 
 }  // namespace mg3m

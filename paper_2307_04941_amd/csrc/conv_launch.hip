@@ -196,7 +196,7 @@ int launch_conv(const Plan& p, const KArgs& a, void* stream, std::string* err, v
     return MG3M_ERR_PLAN;
   }
   KernelFn fn = p.persist ? (fused ? conv_kernel_pt_fused(p.variant, p.tile) : conv_kernel_pt(p.variant, p.tile))
-                : p.b3    ? (fused ? conv_kernel_b3_fused(p.tile) : conv_kernel_b3(p.tile))
+                : p.b3    ? (fused ? conv_kernel_b3_fused(p.b3_load, p.tile) : conv_kernel_b3(p.b3_load, p.tile))
                 : p.acc64 ? kernel64_for(p.variant, p.tile)
                           : (fused ? kernel_fused_for(p.variant, p.tile) : kernel_for(p.variant, p.tile));
   if (fn == nullptr) {

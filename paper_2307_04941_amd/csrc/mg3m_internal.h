@@ -158,17 +158,30 @@ inline constexpr TileDesc kTiles64[kNumTiles64] = {
 // Tile menu of the kernel that takes fp32 products as bf16 part products
 // (conv_b3.h), one-tap HWCN shapes only.  regs as above; eff is the fraction of
 // its peak (bf16 MFMA / 6) that the model charges.
-constexpr int kNumTilesB3 = 8;
+constexpr int kNumTilesB3 = 9;
 inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
-    {128, 128, 32, 1, 4, 254, 0.575},                 // 0
+    {128, 128, 32, 1, 4, 253, 0.585},                 // 0
     {128, 256, 32, 1, 8, 244, 0.61},                  // 1: eight waves sharing one filter tile
-    {64, 256, 64, 1, 8, 185, 0.50},                   // 2: 64 output channels
-    {64, 128, 64, 1, 4, 187, 0.43},                   // 3
-    {64, 128, 32, 1, 4, 178, 0.43},                   // 4
-    {64, 64, 32, 1, 4, 114, 0.62, 0, 0, 0.64},        // 5
-    {64, 64, 64, 1, 4, 123, 0.40},                    // 6
-    {32, 128, 32, 1, 4, 131, 0.39},                   // 7: small layers
+    {64, 256, 64, 1, 8, 186, 0.50},                   // 2: 64 output channels
+    {64, 128, 64, 1, 4, 187, 0.44},                   // 3
+    {64, 128, 32, 1, 4, 178, 0.44},                   // 4
+    {64, 64, 32, 1, 4, 114, 0.62, 0, 0, 0.60},        // 5
+    {64, 64, 64, 1, 4, 127, 0.372},                   // 6
+    {32, 128, 32, 1, 4, 132, 0.37},                   // 7: small layers
+    {64, 256, 32, 1, 8, 181, 0.50},                   // 8: as 2, for the forms of 32-deep stages only
 };
+// Its operand addressing (conv_b3.h), and the tiles each form is built for:
+// the group forms take 32-deep stages in which a thread stages at most one
+// group of eight filter rows.
+enum B3Load : int { kB3Slab = 0, kB3SlabW = 1, kB3Group = 2, kB3GroupN = 3, kB3GroupC = 4, kB3Row = 5, kB3RowN = 6 };
+constexpr bool b3_groups(int ld) { return ld >= kB3Group; }
+constexpr bool b3_built(int ld, int tile) {
+  const TileDesc& t = kTilesB3[tile];
+  if (b3_groups(ld)) return t.kt == 32 && t.mt < 128;
+  // (the other tiles' NCHW form spills scalar registers to memory)
+  if (ld == kB3SlabW) return tile == 1 || tile == 2 || tile == 5;
+  return tile != 8;
+}
 // LDS bytes: two stages of the filter in three bf16 parts.
 constexpr int lds_bytes_for_b3(const TileDesc& t) { return 2 * 3 * 2 * t.kt * t.mt; }
 
@@ -192,6 +205,7 @@ struct Plan {
   int layout;
   int acc64;                // 1: the fp64-accumulating kernel (tile indexes kTiles64)
   int b3;                   // 1: the kernel of bf16 part products (tile indexes kTilesB3)
+  int b3_load;              // its operand addressing (B3Load)
   int tile;                 // index into kTiles (kTiles64 when acc64)
   TileDesc t;
   int k_tiles;              // ceil(Kg / kt)
@@ -316,8 +330,10 @@ KernelFn conv_kernel64_nchw(int variant, int tile);
 
 // Kernels of bf16 part products by tile, plain and with the fused output
 // stage: conv_b3*.hip.
-KernelFn conv_kernel_b3(int tile);
-KernelFn conv_kernel_b3_fused(int tile);
+KernelFn conv_kernel_b3(int load, int tile);
+KernelFn conv_kernel_b3_fused(int load, int tile);
+KernelFn conv_kernel_b3_any(int load, int tile);         // conv_b3_any.hip: the group and row forms
+KernelFn conv_kernel_b3_any_fused(int load, int tile);   // conv_b3_any_fused.hip
 
 // Kernel launchers (conv_launch.hip, pool.hip).
 // start / stop: hipEvent_t handles (or null) that take the main kernel's own

@@ -38,9 +38,9 @@ constexpr int kMaxWavesPerSimd = 8;
 constexpr double kStreamBytesPerS = 4.0e12;
 constexpr double kLaunchUs = 3.0;
 constexpr double kRoundUs = 2.0;
+constexpr double kTailLaunchUsB3 = 4.5;      // second launch of a b3 plan: launch gap, reduction and its cold partials
 constexpr double kUtilBase = 0.5, kUtilPerWave = 0.1;
 constexpr double kUtilBaseB3 = 0.5, kUtilPerWaveB3 = 0.25;   // the kernel of bf16 part products: two waves fill it
-constexpr double kStepUsB3 = 0.6;             // its k-step of 32 rows with one work-group on a CU (load, split, MFMA)
 // Persistent plans (conv_igemm_f32_pt), measured on MI355X against the same
 // tile's data-parallel plan: its main loop (run-time LDS buffer parity, one
 // copy of the stage code) runs at 0.92 of the tile's rate on deep reductions
@@ -58,6 +58,12 @@ constexpr double kStreamBytesPerSPersist = 4.8e12;
 // total 18714 us against 18823 before and 18696 for the faster of the two on
 // every layer.
 constexpr double kNchwStridedFactor = 0.6;
+// In NCHW the kernel of bf16 part products loads 16 output pixels at a time,
+// which on rows shorter than that touch two input rows: 512 channels at 14x14
+// then run as fast on HWCN copies (N = 64: 281 against 283 us), where wider rows
+// are faster in place (28x28: 963 against 1005; 56x56, 256 channels, N = 32: 493
+// against 551).
+constexpr double kNchwShortRowFactorB3 = 0.95;
 
 long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
@@ -317,6 +323,27 @@ bool shape_plan(const ConvShape& s, Family f, int tile, int sched, long long par
   return true;
 }
 
+// The operand addressing forms of the kernel of bf16 part products: speed
+// against the one-tap form when the chip is full, and the time a work-group
+// alone on its CU takes for a k-step of 32 rows beyond its MFMAs (loads, splits,
+// the barrier).  Fitted to timings of every b3 tile on the catalogue layers and
+// on nineteen odd-sized ones (batches of 1 to 33, 3 to 384 channels).
+double b3_factor(int load, const TileDesc& t) {
+  switch (load) {
+    case kB3Slab: return 1.0;
+    case kB3SlabW: return 0.9;
+    case kB3Group: return t.mt == 64 && t.nt >= 128 ? 1.0 : 0.9;
+    case kB3GroupN: return t.mt == 32 ? 0.5 : 0.8;      // a load per column and row: half as many products to each
+    case kB3GroupC: return 0.85;
+    case kB3Row: return 0.68;
+    default: return t.mt == 32 ? 0.45 : 0.62;
+  }
+}
+double b3_step_us(int load, const TileDesc& t) {
+  constexpr double alone[] = {0.55, 0.7, 0.6, 0.95, 0.55, 0.85, 1.1};     // by B3Load
+  return (alone[load] + 2.0 * t.mt * t.nt * 32 / (kFlopPerClkCUB3 * kClockHz) * 1e6) * t.kt / 32;
+}
+
 // The selector's predicted time for a plan (microseconds).  Work-groups are
 // dispatched in order, whole tiles first and tail runs after them.  In each
 // phase the busiest CU runs ceil(work-groups / 256) of them, each costing its
@@ -329,19 +356,20 @@ double predict_us(const ConvShape& s, const Plan& p) {
   const int occ = resident_wgs(t, family(p), p.persist ? p.variant : -1);
   const double rate = p.acc64 ? kFlopPerClkCU64 : p.b3 ? kFlopPerClkCUB3 : kFlopPerClkCU;
   const double tile_flops = 2.0 * t.mt * t.nt * (double)t.kt;
-  const bool multitap = s.R * s.S > 1 && s.C >= 2 * t.kt;
+  const bool multitap = s.R * s.S > 1 && (p.b3 || s.C >= 2 * t.kt);
   auto phase = [&](long long wgs, int k_tiles) {
     if (wgs <= 0) return 0.0;
     const long long per_cu = cdiv(wgs, kCUs);
     const double waves_per_simd = (double)std::min<long long>(per_cu, occ) * t.wm * t.wn / 4.0;
     const double util = p.b3 ? std::min(1.0, kUtilBaseB3 + kUtilPerWaveB3 * waves_per_simd)
                              : std::min(1.0, kUtilBase + kUtilPerWave * waves_per_simd);
-    const double eff = t.eff * variant_factor(p.variant) * util * (multitap ? t.eff_multitap : 1.0) *
+    const double eff = t.eff * (p.b3 ? b3_factor(p.b3_load, t) : variant_factor(p.variant)) * util * (multitap ? t.eff_multitap : 1.0) *
                        (p.persist ? kPersistEff : 1.0) *
-                       (s.layout == kNCHW && p.b_mode == kBVecW && s.sw > 1 ? kNchwStridedFactor : 1.0);
+                       (p.b3 && s.layout == kNCHW && s.Wo < 16 ? kNchwShortRowFactorB3 : 1.0) *
+                       (s.layout == kNCHW && !p.b3 && p.b_mode == kBVecW && s.sw > 1 ? kNchwStridedFactor : 1.0);
     double us = (double)per_cu * tile_flops * k_tiles / (rate * kClockHz * eff) * 1e6;
     // few work-groups: no faster than the chain of their k-steps
-    if (p.b3) us = std::max(us, (double)cdiv(per_cu, occ) * k_tiles * t.kt / 32 * kStepUsB3);
+    if (p.b3) us = std::max(us, (double)cdiv(per_cu, occ) * k_tiles * b3_step_us(p.b3_load, t));
     return us + (p.persist ? 1.0 : (double)cdiv(per_cu, occ)) * kRoundUs;
   };
   const int run_k = p.tail_wgs > 0 ? p.sk_q + (p.sk_r > 0 ? 1 : 0) : 0;
@@ -355,7 +383,7 @@ double predict_us(const ConvShape& s, const Plan& p) {
   double est = std::max(t_comp, t_mem) + kLaunchUs;
   if (p.tail_tiles > 0) {
     const double tail_out = 4.0 * (double)p.tail_tiles * t.mt * t.nt;
-    est += (part_bytes + tail_out) / kStreamBytesPerS * 1e6 + kLaunchUs;
+    est += (part_bytes + tail_out) / kStreamBytesPerS * 1e6 + (p.b3 ? kTailLaunchUsB3 : kLaunchUs);
   }
   if (p.wt_bytes > 0) est += 2.0 * (double)p.wt_bytes / kStreamBytesPerS * 1e6 + kLaunchUs;
   return est;
@@ -449,6 +477,30 @@ void choose_modes(const ConvShape& s, bool x16, bool w16, bool y16, Plan* p, boo
   if (p->acc64) p->e_mode = kEElem;
 }
 
+// Operand addressing of the kernel of bf16 part products for a plan whose
+// tile and modes are set; false where no form is built for it.  By the
+// narrowest that applies: a filter tap per stage where the channels fill whole
+// stages, groups of eight channels, single rows of the reduction; and a lane's
+// columns as one load where four batch elements lie together.
+static bool choose_b3(const ConvShape& s, bool x16, bool y16, Plan* p) {
+  const bool vec = s.N % 4 == 0 && x16 && y16;
+  if (s.layout == kNCHW) {
+    if (p->variant != kVarNchwTap) return false;
+    p->b3_load = kB3SlabW;
+  } else if (vec && s.C % p->t.kt == 0) {
+    p->b3_load = kB3Slab;
+    if (s.K % 4 != 0 || p->b_mode == kBScalar) p->b_mode = kBVecNTap;   // the filter is read by elements
+  } else if (s.C % 8 == 0) {
+    p->b3_load = vec ? kB3Group : s.N == 1 && x16 ? kB3GroupC : kB3GroupN;
+  } else {
+    p->b3_load = vec ? kB3Row : kB3RowN;
+  }
+  if (p->b3_load >= kB3Group) p->b_mode = vec ? kBVecN : p->b3_load == kB3GroupC ? kBVecC : kBScalar;
+  p->a_mode = kAVecMB3;
+  p->e_mode = kEElem;
+  return b3_built(p->b3_load, p->tile);
+}
+
 int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x16, bool w16,
               bool y16, Plan* p, std::string* err, size_t ws_cap) {
   Override o;
@@ -476,11 +528,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // which stage through VGPRs
     const bool dma_ok = !c.acc64 && !c.t.m16;
     choose_modes(sv, via || x16, via || w16, via || y16, &c, dma_ok && o.dma != 0);
-    if (c.b3) {
-      // the one-tap HWCN shapes with C a multiple of its kt, 16-byte aligned output
-      if ((c.variant != kVarHwcnVecNTapDma && c.variant != kVarHwcnVecNTap) || !(via || y16) || o.dma == 1) return;
-      c.a_mode = kAVecMB3;
-    }
+    if (c.b3 && (o.dma == 1 || !choose_b3(sv, via || x16, via || y16, &c))) return;
     if (via) {
       auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
       c.via_hwcn = 1;

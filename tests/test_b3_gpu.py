@@ -17,33 +17,56 @@ pytestmark = pytest.mark.gpu
 
 TILES = ["tile=128x128,waves=1x4,kt=32", "tile=128x256,waves=1x8,kt=32", "tile=64x256,waves=1x8,kt=64",
          "tile=64x128,waves=1x4,kt=64", "tile=64x128,waves=1x4,kt=32", "tile=64x64,waves=1x4,kt=32",
-         "tile=64x64,waves=1x4,kt=64", "tile=32x128,waves=1x4,kt=32"]
+         "tile=64x64,waves=1x4,kt=64", "tile=32x128,waves=1x4,kt=32", "tile=64x256,waves=1x8,kt=32"]
 
-# (N, C, H, W, K, R, S, stride, pad): one stage; an odd count; 3x3 with ragged
-# rows and columns; stride 2 with an even window
-SHAPES = [(4, 64, 3, 5, 20, 1, 1, 1, 0), (8, 192, 7, 5, 132, 1, 1, 1, 0), (4, 64, 13, 11, 68, 3, 3, 1, 1),
-          (12, 128, 9, 10, 36, 2, 3, 2, 1)]
+# (N, C, H, W, K, R, S, stride, pad), layout, misalign.  One stage; an odd
+# count; 3x3 with ragged rows and columns; stride 2 with an even window: one
+# tap per stage.  Then groups of eight channels (batch vectors, any batch, one
+# image, misaligned buffers), single rows (three channels; any batch; one
+# channel), and NCHW.
+SHAPES = [((4, 64, 3, 5, 20, 1, 1, 1, 0), "HWCN", 0), ((8, 192, 7, 5, 132, 1, 1, 1, 0), "HWCN", 0),
+          ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", 0), ((12, 128, 9, 10, 36, 2, 3, 2, 1), "HWCN", 0),
+          ((4, 16, 9, 7, 36, 3, 3, 1, 1), "HWCN", 0), ((8, 72, 5, 6, 67, 2, 5, 1, 2), "HWCN", 0),
+          ((3, 24, 8, 9, 20, 3, 3, 1, 1), "HWCN", 0), ((2, 64, 6, 5, 96, 3, 1, 3, 0), "HWCN", 0),
+          ((1, 40, 11, 6, 70, 3, 3, 2, 1), "HWCN", 0), ((1, 64, 9, 9, 64, 1, 1, 1, 0), "HWCN", 0),
+          ((4, 64, 7, 6, 40, 3, 3, 1, 1), "HWCN", 1), ((1, 16, 7, 6, 20, 3, 3, 1, 1), "HWCN", 1),
+          ((8, 3, 10, 9, 68, 5, 3, 2, 2), "HWCN", 0), ((4, 75, 6, 5, 40, 3, 3, 1, 1), "HWCN", 0),
+          ((7, 13, 6, 5, 33, 3, 2, 1, 1), "HWCN", 0), ((1, 1, 9, 8, 5, 3, 3, 1, 0), "HWCN", 0),
+          ((5, 2, 12, 3, 70, 1, 3, 1, 3), "HWCN", 0),
+          ((3, 64, 9, 7, 68, 3, 3, 1, 1), "NCHW", 0), ((2, 32, 5, 6, 132, 2, 3, (2, 1), (0, 2)), "NCHW", 0)]
 
 
-def _is_b3(shape, plan):
-    return "a=vec_m_b3" in mg3m.conv2d_fwd_f32_plan_string(*shape, "HWCN", plan)
+def _plan_string(shape, layout, plan):
+    N, C, H, W, K, R, S, st, pd = shape
+    if isinstance(st, tuple):
+        return ""
+    return mg3m.conv2d_fwd_f32_plan_string(N, C, H, W, K, R, S, st, pd, layout, plan)
 
 
-@pytest.mark.parametrize("tile", TILES)
-def test_every_b3_tile_exact(tile):
-    for si, shape in enumerate(SHAPES):
-        x, w, st, pd = make(shape, 3300 + si, "HWCN", dist="int")
-        acc, _ = oracle.conv2d(x, w, st, pd, "HWCN")
+def _is_b3(shape, plan, layout="HWCN"):
+    return "a=vec_m_b3" in mg3m.conv2d_fwd_f32_plan_string(*shape, layout, plan)
+
+
+@pytest.mark.parametrize("case", range(len(SHAPES)))
+def test_every_b3_tile_exact(case):
+    shape, layout, misalign = SHAPES[case]
+    x, w, st, pd = make(shape, 3300 + case, layout, dist="int")
+    acc, _ = oracle.conv2d(x, w, st, pd, layout)
+    ran = set()
+    for tile in TILES:
         for sched in ("split=1", "split=2", "split=5", "sk=7"):
-            plan = f"{tile},{sched}"
+            plan = f"{tile},{sched}" + (",via=none" if layout == "NCHW" else "")
             try:
-                assert _is_b3(shape, plan), plan
-            except mg3m.Mg3mError:
-                assert sched == "sk=7", plan         # fewer k-tiles than work-groups, or more tiles
+                text = _plan_string(shape, layout, plan)
+                assert not text or "a=vec_m_b3" in text, text
+                say(f"b3 {plan} {layout} {shape}")
+                y = run_gpu(x, w, st, pd, layout, plan=plan, misalign=misalign)
+            except mg3m.Mg3mError as e:
+                assert e.status == 7, e          # the tile is not built for this form, or sk does not apply
                 continue
-            say(f"b3 {plan} {shape}")
-            y = run_gpu(x, w, st, pd, "HWCN", plan=plan)
+            ran.add(tile)
             assert np.array_equal(y, acc.astype(np.float32)), f"{shape} {plan}: not bit-exact"
+    assert len(ran) >= 2, ran
 
 
 @pytest.mark.parametrize("Kg", [(64, 1), (64, 3), (512, 3)])
@@ -108,6 +131,28 @@ def _special(kind, x, w):
         x *= np.float32(2.0**-70)
         w *= np.float32(2.0**-70)
     return x, w
+
+
+@pytest.mark.parametrize("shape,plan", [((4, 16, 6, 5, 68, 3, 3, 1, 1), "tile=64x128,waves=1x4,kt=32"),
+                                        ((1, 40, 6, 5, 36, 3, 3, 1, 1), "tile=64x64,waves=1x4,kt=32"),
+                                        ((5, 24, 6, 5, 36, 3, 3, 1, 1), "tile=32x128,waves=1x4,kt=32"),
+                                        ((4, 3, 6, 5, 68, 3, 3, 1, 1), "tile=64x64,waves=1x4,kt=32"),
+                                        ((3, 5, 6, 5, 36, 3, 3, 1, 1), "tile=64x256,waves=1x8,kt=32")])
+def test_b3_range_check_other_forms(shape, plan):
+    """One infinity in x and in w: exactly the outputs they reach are not finite,
+    the others stay within the fp32 bound (the second computation addresses its
+    operands by the same forms)."""
+    assert _is_b3(shape, plan)
+    x, w, st, pd = make(shape, 3650, "HWCN")
+    clean, mag = oracle.conv2d(x, w, st, pd, "HWCN")
+    x[3, 2, shape[1] - 1, 0] = np.inf
+    w[1, 2, 0, 3] = np.inf
+    y = run_gpu(x, w, st, pd, "HWCN", plan=plan)
+    ref = run_gpu(x, w, st, pd, "HWCN", plan="tile=64x64,waves=1x1,kt=16")
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
+    assert np.isinf(y).any() and np.isfinite(y).any()
+    fin = np.isfinite(ref)
+    assert np.all(np.abs(y[fin] - clean[fin]) <= 1e-5 * mag[fin])
 
 
 @pytest.mark.parametrize("kind", ["inf", "nan", "inf_filter", "near_max", "overflow", "tiny", "tiny_sums"])

@@ -133,14 +133,22 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    of one shape (64x64 comes as 1x1 with kt=16 and 2x2 with
  *                    kt=32), so the tile, waves and kt of a plan string read back
  *                    as an override for the same tile
- *                    Shapes of the one-tap HWCN loader (HWCN or via=hwcn, N and K
- *                    multiples of 4, C a multiple of kt, aligned buffers) also have
- *                    tiles whose fp32 products run as bf16 part products, exact in
+ *                    Further tiles take fp32 products as bf16 part products, exact in
  *                    both operands (a=vec_m_b3 in plan strings), told apart by their
  *                    waves: 128x128,waves=1x4,kt=32; 128x256,waves=1x8,kt=32;
  *                    64x256,waves=1x8,kt=64; 64x128,waves=1x4,kt=64 and kt=32;
- *                    64x64,waves=1x4,kt=32 and kt=64; 32x128,waves=1x4,kt=32.
- *                    They are not persistent and dma=1 excludes them
+ *                    64x64,waves=1x4,kt=32 and kt=64; 32x128,waves=1x4,kt=32 for
+ *                    shapes of the one-tap HWCN loader (HWCN or via=hwcn, N a multiple
+ *                    of 4, C of kt, aligned x and y; any K); of these 128x256,
+ *                    64x256 and 64x64,kt=32 in NCHW where the filter copy applies (K
+ *                    a multiple of 4, C of kt, unit horizontal stride, several taps);
+ *                    and the 64- and 32-row tiles with kt=32, and
+ *                    64x256,waves=1x8,kt=32, for HWCN shapes of any N, C and K.
+ *                    64x64,waves=1x2,kt=32 is the persistent one of them for 1x1
+ *                    filters: HWCN, N a multiple of 4, C of 64 and at most 384, more
+ *                    than 256 tiles, aligned x and y; its work-groups of twelve waves
+ *                    keep the filter in LDS.  dma=1 excludes them all, and so does
+ *                    persist=, but for that last one with its waves and persist=1
  *   kt=16|32|64      reduction depth staged per step (default 16 with a tile)
  *   split=<n>        share every tile's reduction out over n work-groups per tile
  *                    (1..64, clamped to the tile's k-tiles; 1 = no split)
@@ -340,8 +348,11 @@ typedef struct mg3m_plan_info {
     double est_us;            /* the selector's predicted time */
     int layout;               /* MG3M_LAYOUT_* */
     int a_mode, b_mode;       /* operand loader variant of the main kernel (its template arguments);
-                                 a_mode 3: the kernel of bf16 part products, for the shapes of b_mode
-                                 6 (3 with dma=0; its patches go straight to registers either way) */
+                                 a_mode 3: the kernels of bf16 part products; b_mode then
+                                 names the shape class (6, or 3 with dma=0: a filter tap
+                                 per stage; 5: the same in NCHW; 0, 1, 2: batch vectors,
+                                 one image, any other), its patches go straight to
+                                 registers */
     int e_mode;               /* epilogue store mode */
     int persistent;           /* 1: grid work-groups loop over the dp_tiles whole tiles */
     int via_hwcn;             /* 1: an NCHW call run as HWCN on copies in the workspace (layout, a_mode,

@@ -551,6 +551,62 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds, int 
   store(acc, m0, n0, wn * C::WTN, g4, q);
 }
 
+// A lane's finished rows (16*i + e from row_l on) of SW columns from n on
+// (accumulator columns u .. u+SW-1) to y, with the fused output stage.  Rows
+// and columns outside y go to the out-of-range offset.
+template <int LAYOUT, int TM, int TN, int SW, bool FUSE>
+__device__ __forceinline__ void store_cols_b3(const KArgs& a, __amdgpu_buffer_rsrc_t yr, __amdgpu_buffer_rsrc_t ar,
+                                              bool has_add, f32x4 (&acc)[TM][TN], int u, int row_l, int n) {
+  unsigned rs4 = 4u * (unsigned)a.mstride;
+  asm volatile("" : "+s"(rs4));
+  const int rows_left = a.Mg - row_l;
+  const bool col_ok = n < a.Ng;
+  const unsigned voff = 4u * (unsigned)(out_colbase<LAYOUT>(a, n) + row_l * a.mstride);
+  auto offset = [&](int i, int e) {
+    const bool ok = col_ok & (i * 16 + e < rows_left);
+    return ok ? voff + (unsigned)(i * 16 + e) * rs4 : kOOB;
+  };
+  if constexpr (FUSE) {
+    // every load of add is in flight before the first is used (they fit the
+    // registers that the small products' sums leave).  Loaded one by one, each
+    // waited for the store before it, which may go to the same memory:
+    // 64 -> 256 channels at 56x56, N = 64: 228 us, now 112 (one form's 128x128
+    // tiles).
+    if (has_add) {
+      float d[TM][4][SW];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bload_w<SW>(ar, offset(i, e), 0u, d[i][e]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < SW; ++j) acc[i][u + j][e] += d[i][e][j];
+    }
+    if (a.relu != 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < SW; ++j)
+            if (acc[i][u + j][e] < 0.f) acc[i][u + j][e] = 0.f;     // NaN kept
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float v[SW];
+#pragma unroll
+      for (int j = 0; j < SW; ++j) v[j] = acc[i][u + j][e];
+      bstore_w<SW>(yr, offset(i, e), 0u, v);
+    }
+}
+
 // Schedule and tails as conv_igemm_f32: whole tiles grouped per XCD, then the
 // tail work-groups, whose pieces (split, or stream-K runs of up to two) leave
 // tile-local partials for the tail reduction.
@@ -597,40 +653,10 @@ void conv_igemm_b3(KArgs a) {
           const __amdgpu_buffer_rsrc_t yr = make_rsrc(a.y, a.y_bytes);
           const bool has_add = FUSE && a.add != nullptr;
           const __amdgpu_buffer_rsrc_t ar = make_rsrc(has_add ? a.add : a.y, a.y_bytes);
-          unsigned rs4 = 4u * (unsigned)a.mstride;
-          asm volatile("" : "+s"(rs4));
-          const int row_l = m0 + 4 * g4, rows_left = a.Mg - row_l;
 #pragma unroll
-          for (int u = 0; u < NS; ++u) {
-            const int n = n0 + wcol + (kVec ? q * TN : 16 * u + q);
-            const bool col_ok = n < a.Ng;
-            const unsigned voff =
-                4u * (unsigned)(out_colbase<LD == kB3SlabW ? kNCHW : kHWCN>(a, n) + row_l * a.mstride);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const bool ok = col_ok & (i * 16 + e < rows_left);
-                const unsigned off = ok ? voff + (unsigned)(i * 16 + e) * rs4 : kOOB;
-                float v[SW];
-#pragma unroll
-                for (int j = 0; j < SW; ++j) v[j] = acc[i][u + j][e];
-                if constexpr (FUSE) {
-                  float d[SW];
-                  if (has_add) {
-                    bload_w<SW>(ar, off, 0u, d);
-#pragma unroll
-                    for (int j = 0; j < SW; ++j) v[j] += d[j];
-                  }
-                  if (a.relu != 0) {
-#pragma unroll
-                    for (int j = 0; j < SW; ++j)
-                      if (v[j] < 0.f) v[j] = 0.f;     // NaN kept
-                  }
-                }
-                bstore_w<SW>(yr, off, 0u, v);
-              }
-          }
+          for (int u = 0; u < NS; ++u)
+            store_cols_b3<LD == kB3SlabW ? kNCHW : kHWCN, TM, TN, SW, FUSE>(
+                a, yr, ar, has_add, acc, u, m0 + 4 * g4, n0 + wcol + (kVec ? q * TN : 16 * u + q));
         });
     run.it += nk;
     if (whole || run.it >= run.end) return;

@@ -1308,25 +1308,34 @@ __device__ __forceinline__ void store_tile_f32_buf(const KArgs& a, floatx16 (&ac
     const bool col_ok = n < a.Ng;
     const unsigned voff = 4u * (unsigned)(out_colbase<LAYOUT>(a, n) + row_l * a.mstride);
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
+    for (int i = 0; i < C::TM; ++i) {
+      auto offset = [&](int r) {                    // row r from the lane's first row
+        const bool ok = col_ok & (r < rows_left);
+        return ok ? voff + (unsigned)r * rs4 : kOOB;
+      };
+      // fused output stage: add (same layout as y) read through its own buffer
+      // resource at the stores' offsets, a block's sixteen loads in flight
+      // before its first store: one by one, each load waited for the store
+      // before it, which may go to the same memory.  ReLU keeps NaN.
+      float d[FUSE ? 16 : 1];
+      if constexpr (FUSE) {
+        if (has_add) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const unsigned o = voff + (unsigned)(i * 32 + 8 * g) * rs4;
+          for (int e = 0; e < 16; ++e) d[e] = bload1(ar, offset(i * 32 + 8 * (e / 4) + e % 4));
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = i * 32 + 8 * g + e;         // row offset from the lane's first row
-          const bool ok = col_ok & (r < rows_left);
-          const unsigned off = ok ? o + (unsigned)e * rs4 : kOOB;
-          float v = acc[i][j][4 * g + e];
-          if constexpr (FUSE) {
-            // fused output stage: add (same layout as y) read through its own
-            // buffer resource at the store's offset; ReLU keeps NaN
-            if (has_add) v += bload1(ar, off);
-            if (a.relu != 0 && v < 0.f) v = 0.f;
-          }
-          bstore1(yr, off, 0u, v);
+          for (int e = 0; e < 16; ++e) acc[i][j][e] += d[e];
         }
       }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        float v = acc[i][j][e];
+        if constexpr (FUSE) {
+          if (a.relu != 0 && v < 0.f) v = 0.f;
+        }
+        bstore1(yr, offset(i * 32 + 8 * (e / 4) + e % 4), 0u, v);
+      }
+    }
   }
 }
 

@@ -186,8 +186,9 @@ int launch_conv(const Plan& p, const KArgs& a, void* stream, std::string* err, v
     *err = "internal: stream-K tail plan for a kernel without multi-piece runs";
     return MG3M_ERR_PLAN;
   }
-  if (p.persist && (p.acc64 || p.b3 || p.tail_wgs != 0 || p.grid > p.dp_tiles)) {
-    *err = "internal: persistent plans take whole tiles of the fp32 kernel only";
+  if (p.persist && (p.acc64 || p.tail_wgs != 0 || p.grid > p.dp_tiles ||
+                    (p.b3 && (p.grid % 8 != 0 || a.C % 64 != 0 || a.C > kB3ResMaxC || a.R * a.S != 1)))) {
+    *err = "internal: inconsistent persistent plan";
     return MG3M_ERR_PLAN;
   }
   if (p.dp_tiles < 0 || p.tail_wgs < 0 || (!p.persist && p.grid != (long long)p.dp_tiles + p.tail_wgs) ||
@@ -195,7 +196,8 @@ int launch_conv(const Plan& p, const KArgs& a, void* stream, std::string* err, v
     *err = "internal: grid out of range or inconsistent";
     return MG3M_ERR_PLAN;
   }
-  KernelFn fn = p.persist ? (fused ? conv_kernel_pt_fused(p.variant, p.tile) : conv_kernel_pt(p.variant, p.tile))
+  KernelFn fn = p.persist && p.b3 ? conv_kernel_b3_res(fused)
+                : p.persist ? (fused ? conv_kernel_pt_fused(p.variant, p.tile) : conv_kernel_pt(p.variant, p.tile))
                 : p.b3    ? (fused ? conv_kernel_b3_fused(p.b3_load, p.tile) : conv_kernel_b3(p.b3_load, p.tile))
                 : p.acc64 ? kernel64_for(p.variant, p.tile)
                           : (fused ? kernel_fused_for(p.variant, p.tile) : kernel_for(p.variant, p.tile));
@@ -209,12 +211,12 @@ int launch_conv(const Plan& p, const KArgs& a, void* stream, std::string* err, v
     // (no separate event packets around it on the stream)
     KArgs ka = a;
     void* args[] = {&ka};
-    e = hipExtLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)p.grid), dim3(p.t.wm * p.t.wn * 64),
+    e = hipExtLaunchKernel(reinterpret_cast<const void*>(fn), dim3((unsigned)p.grid), dim3(plan_threads(p)),
                            args, 0, static_cast<hipStream_t>(stream), static_cast<hipEvent_t>(start),
                            static_cast<hipEvent_t>(stop), 0);
     if (e == hipSuccess) e = hipGetLastError();
   } else {
-    hipLaunchKernelGGL(fn, dim3((unsigned)p.grid), dim3(p.t.wm * p.t.wn * 64), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(fn, dim3((unsigned)p.grid), dim3(plan_threads(p)), 0, (hipStream_t)stream, a);
     e = hipGetLastError();
   }
   if (e != hipSuccess) {

@@ -15,9 +15,9 @@ enum Layout : int { kHWCN = 0, kNCHW = 1 };
 //   A (filter):        kAVecM   16-byte vectors along OC   (HWCN, K % 4 == 0)
 //                      kAVecK   16-byte vectors along Kg   (NCHW, Kg % 4 == 0)
 //                      kAScalar single elements            (any)
-//                      kAVecMB3 not a loader of the fp32 kernels: the kernel of
-//                               conv_b3.h (products as bf16 parts), which takes
-//                               the shapes of kBVecNTap with C % 32 == 0
+//                      kAVecMB3 not a loader of the fp32 kernels: the kernels of
+//                               bf16 part products, whose operand forms B3Load
+//                               lists
 //   B (input patches): kBVecNTap 16-byte vectors along the batch, one filter tap
 //                               per staged slab (HWCN, N % 4 == 0, C % kt == 0)
 //                      kBVecN   16-byte vectors along the batch (HWCN, N % 4 == 0)
@@ -156,19 +156,22 @@ inline constexpr TileDesc kTiles64[kNumTiles64] = {
 };
 
 // Tile menu of the kernel that takes fp32 products as bf16 part products
-// (conv_b3.h), one-tap HWCN shapes only.  regs as above; eff is the fraction of
-// its peak (bf16 MFMA / 6) that the model charges.
-constexpr int kNumTilesB3 = 9;
+// (conv_b3.h), and last its persistent relative (conv_b3_res.h).  regs as above,
+// of the form kB3Slab (tile 8: kB3Group); eff is the fraction of the peak (bf16
+// MFMA / 6) that the model charges.
+constexpr int kNumTilesB3 = 10;
+constexpr int kTileB3Res = 9;
 inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
     {128, 128, 32, 1, 4, 253, 0.585},                 // 0
     {128, 256, 32, 1, 8, 244, 0.61},                  // 1: eight waves sharing one filter tile
     {64, 256, 64, 1, 8, 186, 0.50},                   // 2: 64 output channels
-    {64, 128, 64, 1, 4, 187, 0.44},                   // 3
+    {64, 128, 64, 1, 4, 186, 0.44},                   // 3
     {64, 128, 32, 1, 4, 178, 0.44},                   // 4
-    {64, 64, 32, 1, 4, 114, 0.62, 0, 0, 0.60},        // 5
-    {64, 64, 64, 1, 4, 127, 0.372},                   // 6
-    {32, 128, 32, 1, 4, 132, 0.37},                   // 7: small layers
+    {64, 64, 32, 1, 4, 113, 0.62, 0, 0, 0.60},        // 5
+    {64, 64, 64, 1, 4, 121, 0.372},                   // 6
+    {32, 128, 32, 1, 4, 130, 0.37},                   // 7: small layers
     {64, 256, 32, 1, 8, 181, 0.50},                   // 8: as 2, for the forms of 32-deep stages only
+    {64, 64, 32, 1, 2, 160, 0.50},                    // 9: the resident-filter kernel (1x1, persistent)
 };
 // Its operand addressing (conv_b3.h), and the tiles each form is built for:
 // the group forms take 32-deep stages in which a thread stages at most one
@@ -177,13 +180,17 @@ enum B3Load : int { kB3Slab = 0, kB3SlabW = 1, kB3Group = 2, kB3GroupN = 3, kB3G
 constexpr bool b3_groups(int ld) { return ld >= kB3Group; }
 constexpr bool b3_built(int ld, int tile) {
   const TileDesc& t = kTilesB3[tile];
-  if (b3_groups(ld)) return t.kt == 32 && t.mt < 128;
+  if (b3_groups(ld)) return t.kt == 32 && t.mt < 128 && tile != kTileB3Res;
   // (the other tiles' NCHW form spills scalar registers to memory)
   if (ld == kB3SlabW) return tile == 1 || tile == 2 || tile == 5;
-  return tile != 8;
+  return tile < 8;
 }
 // LDS bytes: two stages of the filter in three bf16 parts.
 constexpr int lds_bytes_for_b3(const TileDesc& t) { return 2 * 3 * 2 * t.kt * t.mt; }
+// The persistent kernel with the filter in LDS (conv_b3_res.h): one work-group
+// per CU, and up to this many input channels.
+constexpr int kB3ResWaves = 12, kB3ResMaxC = 384;
+constexpr int kB3ResLds = 3 * 2 * kB3ResMaxC * 64;
 
 // Largest tensor the kernels address: byte offsets are 32-bit and 0xFFFFFFC0
 // is reserved as the out-of-range offset that reads as zero.
@@ -227,6 +234,9 @@ struct Plan {
   double pad_eff;
   double est_us;
 };
+
+// Threads per work-group of a plan's kernel.
+inline unsigned plan_threads(const Plan& p) { return 64u * (p.b3 && p.persist ? kB3ResWaves : p.t.wm * p.t.wn); }
 
 // Kernel arguments (passed by value).
 struct KArgs {
@@ -332,6 +342,7 @@ KernelFn conv_kernel64_nchw(int variant, int tile);
 // stage: conv_b3*.hip.
 KernelFn conv_kernel_b3(int load, int tile);
 KernelFn conv_kernel_b3_fused(int load, int tile);
+KernelFn conv_kernel_b3_res(bool fused);                   // conv_b3_res.hip
 KernelFn conv_kernel_b3_any(int load, int tile);         // conv_b3_any.hip: the group and row forms
 KernelFn conv_kernel_b3_any_fused(int load, int tile);   // conv_b3_any_fused.hip
 

@@ -64,6 +64,19 @@ constexpr double kNchwStridedFactor = 0.6;
 // are faster in place (28x28: 963 against 1005; 56x56, 256 channels, N = 32: 493
 // against 551).
 constexpr double kNchwShortRowFactorB3 = 0.95;
+// The resident-filter kernel, against 64x64 tiles of the other on 1x1 layers of
+// 64 to 384 channels: its MFMA efficiency, the filter's way into LDS, and a
+// wave's step of 32 rows alone.  Fitted to which of the two is faster (8x28x28
+// columns, 128 -> 512 channels: 11.8 against 13.8 us; 320 -> 320: 21.1 against 15.4).
+// What a latency-bound launch of the bf16 part product kernel takes less than
+// the model's launch and round (a graph of them: 2.7 us apart from its chain).
+constexpr double kB3AloneUs = 2.0;
+// Stages from which groups of waves share out a tile's reduction: 18 stages 17.4
+// -> 13.9 us (two groups); at 8 there is about a microsecond to gain.
+constexpr int kB3GroupStages = 12;
+constexpr double kB3Small1x1 = 0.63;
+constexpr int kB3WideBatch = 64;
+constexpr double kB3ResStartUs = 2.0, kB3ResEff = 0.75, kB3ResStepUs = 0.6;
 
 long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
@@ -73,7 +86,7 @@ enum Family { kF32 = 0, kF64 = 1, kB3 = 2 };
 const TileDesc& tile_desc(Family f, int i) { return f == kF64 ? kTiles64[i] : f == kB3 ? kTilesB3[i] : kTiles[i]; }
 int num_tiles(Family f) { return f == kF64 ? kNumTiles64 : f == kB3 ? kNumTilesB3 : kNumTiles; }
 int lds_bytes(const TileDesc& t, Family f) {
-  return f == kB3 ? lds_bytes_for_b3(t) : (f == kF64 || t.m16) ? lds_bytes_for64(t) : lds_bytes_for(t);
+  return f == kB3 ? (t.wn == 2 ? kB3ResLds : lds_bytes_for_b3(t)) : (f == kF64 || t.m16) ? lds_bytes_for64(t) : lds_bytes_for(t);
 }
 Family family(const Plan& p) { return p.b3 ? kB3 : p.acc64 ? kF64 : kF32; }
 
@@ -339,9 +352,11 @@ double b3_factor(int load, const TileDesc& t) {
     default: return t.mt == 32 ? 0.45 : 0.62;
   }
 }
-double b3_step_us(int load, const TileDesc& t) {
-  constexpr double alone[] = {0.55, 0.7, 0.6, 0.95, 0.55, 0.85, 1.1};     // by B3Load
-  return (alone[load] + 2.0 * t.mt * t.nt * 32 / (kFlopPerClkCUB3 * kClockHz) * 1e6) * t.kt / 32;
+// Chain of a tile's k_tiles stages (wm groups of waves share them out).
+double b3_chain_us(int load, const TileDesc& t, int k_tiles) {
+  constexpr double alone[] = {0.6, 0.75, 0.7, 0.95, 0.6, 0.85, 1.1};     // by B3Load
+  const double mfma = 2.0 * t.mt * t.nt * 32 / (kFlopPerClkCUB3 * kClockHz) * 1e6;
+  return (cdiv(k_tiles, t.wm) * alone[load] + k_tiles * mfma) * t.kt / 32 - kB3AloneUs;
 }
 
 // The selector's predicted time for a plan (microseconds).  Work-groups are
@@ -353,7 +368,7 @@ double b3_step_us(int load, const TileDesc& t) {
 // partials) once; the tail reduction adds its traffic and a second launch.
 double predict_us(const ConvShape& s, const Plan& p) {
   const TileDesc& t = p.t;
-  const int occ = resident_wgs(t, family(p), p.persist ? p.variant : -1);
+  const int occ = resident_wgs(t, family(p), p.persist && !p.b3 ? p.variant : -1);
   const double rate = p.acc64 ? kFlopPerClkCU64 : p.b3 ? kFlopPerClkCUB3 : kFlopPerClkCU;
   const double tile_flops = 2.0 * t.mt * t.nt * (double)t.kt;
   const bool multitap = s.R * s.S > 1 && (p.b3 || s.C >= 2 * t.kt);
@@ -365,15 +380,30 @@ double predict_us(const ConvShape& s, const Plan& p) {
                              : std::min(1.0, kUtilBase + kUtilPerWave * waves_per_simd);
     const double eff = t.eff * (p.b3 ? b3_factor(p.b3_load, t) : variant_factor(p.variant)) * util * (multitap ? t.eff_multitap : 1.0) *
                        (p.persist ? kPersistEff : 1.0) *
+                       (p.b3 && s.R * s.S == 1 && s.N >= kB3WideBatch && t.mt * t.nt == 64 * 64 ? kB3Small1x1 : 1.0) *
                        (p.b3 && s.layout == kNCHW && s.Wo < 16 ? kNchwShortRowFactorB3 : 1.0) *
                        (s.layout == kNCHW && !p.b3 && p.b_mode == kBVecW && s.sw > 1 ? kNchwStridedFactor : 1.0);
     double us = (double)per_cu * tile_flops * k_tiles / (rate * kClockHz * eff) * 1e6;
-    // few work-groups: no faster than the chain of their k-steps
-    if (p.b3) us = std::max(us, (double)cdiv(per_cu, occ) * k_tiles * b3_step_us(p.b3_load, t));
+    // few work-groups: no faster than the chain of their k-steps, and a four-wave
+    // one alone on its CU just that
+    if (p.b3) {
+      const double chain = (double)cdiv(per_cu, occ) * b3_chain_us(p.b3_load, t, k_tiles);
+      us = per_cu == 1 && t.wm == 1 && t.mt * t.nt <= 64 * 64 ? chain : std::max(us, chain);
+    }
+    if (p.b3) us += t.wm == 1 ? 0.0 : t.wm == 2 ? 1.2 : 4.0;             // adding up the groups' sums
     return us + (p.persist ? 1.0 : (double)cdiv(per_cu, occ)) * kRoundUs;
   };
   const int run_k = p.tail_wgs > 0 ? p.sk_q + (p.sk_r > 0 ? 1 : 0) : 0;
-  const double t_comp = phase(p.dp_tiles, p.k_tiles) + phase(p.tail_wgs, run_k);
+  double t_comp = phase(p.dp_tiles, p.k_tiles) + phase(p.tail_wgs, run_k);
+  if (p.b3 && p.persist) {
+    // blocks of 64x32 dealt out to the waves of a CU; with few of them, no
+    // faster than the chain of a block's steps, twice where a work-group's run
+    // of blocks reaches into a second filter tile
+    const double blocks = (double)cdiv((long long)p.tiles_m * cdiv(s.Ng, 32), 4 * kCUs);
+    const int chains = 32 % p.tiles_m == 0 || p.tiles_m % 32 == 0 ? 1 : 2;
+    t_comp = kB3ResStartUs + std::max(blocks * 2.0 * 64 * 32 * (double)s.Kg / (kFlopPerClkCUB3 / 4 * kClockHz * kB3ResEff) * 1e6,
+                                      chains * (double)s.Kg / 32 * kB3ResStepUs);
+  }
   const double y_bytes = 4.0 * (double)s.Mg * (double)s.Ng;
   const double xw_bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + (double)s.Kg * s.Mg);
   const double part_bytes =
@@ -478,11 +508,12 @@ void choose_modes(const ConvShape& s, bool x16, bool w16, bool y16, Plan* p, boo
 }
 
 // Operand addressing of the kernel of bf16 part products for a plan whose
-// tile and modes are set; false where no form is built for it.  By the
+// tile and modes are set; false where no form is built for it (named: the
+// override names its waves).  By the
 // narrowest that applies: a filter tap per stage where the channels fill whole
 // stages, groups of eight channels, single rows of the reduction; and a lane's
 // columns as one load where four batch elements lie together.
-static bool choose_b3(const ConvShape& s, bool x16, bool y16, Plan* p) {
+static bool choose_b3(const ConvShape& s, bool x16, bool y16, bool named, Plan* p) {
   const bool vec = s.N % 4 == 0 && x16 && y16;
   if (s.layout == kNCHW) {
     if (p->variant != kVarNchwTap) return false;
@@ -498,6 +529,13 @@ static bool choose_b3(const ConvShape& s, bool x16, bool y16, Plan* p) {
   if (p->b3_load >= kB3Group) p->b_mode = vec ? kBVecN : p->b3_load == kB3GroupC ? kBVecC : kBScalar;
   p->a_mode = kAVecMB3;
   p->e_mode = kEElem;
+  // the persistent kernel: 1x1, the filter's channels in LDS, pairs of 32-deep
+  // steps, and a work-group on every CU (its share of the tiles is worked out
+  // from the grid)
+  if (p->persist)
+    return p->tile == kTileB3Res && p->b3_load == kB3Slab && s.R * s.S == 1 && s.C % 64 == 0 && s.C <= kB3ResMaxC &&
+           p->dp_tiles > kCUs && p->grid <= kCUs;
+  if (p->t.wm > 1 && p->k_tiles < kB3GroupStages && !named) return false;
   return b3_built(p->b3_load, p->tile);
 }
 
@@ -528,7 +566,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // which stage through VGPRs
     const bool dma_ok = !c.acc64 && !c.t.m16;
     choose_modes(sv, via || x16, via || w16, via || y16, &c, dma_ok && o.dma != 0);
-    if (c.b3 && (o.dma == 1 || !choose_b3(sv, via || x16, via || y16, &c))) return;
+    if (c.b3 && (o.dma == 1 || !choose_b3(sv, via || x16, via || y16, o.wm > 0, &c))) return;
     if (via) {
       auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
       c.via_hwcn = 1;
@@ -541,11 +579,11 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // 32x32x2 fp32 kernel with the one-tap HWCN loader has it)
     if (c.tail_wgs > 0 && c.sk_s == 0 && (c.acc64 || c.t.m16 || !(c.b3 || tail_runs_multi(c.b_mode)))) return;
     // the persistent kernel is built for the batch-vector HWCN loaders only
-    if (c.persist && (c.acc64 || c.b3 || !persist_built(c.variant, c.t))) return;
+    if (c.persist && !c.b3 && (c.acc64 || !persist_built(c.variant, c.t))) return;
     if (c.persist && sp == 0) {
       // the selector's persistent plans fill every slot the kernel's
       // occupancy allows, and only pay off with more tiles than that
-      const long long slots = (long long)kCUs * resident_wgs(c.t, kF32, c.variant);
+      const long long slots = (long long)kCUs * resident_wgs(c.t, f, c.b3 ? -1 : c.variant);
       if (c.dp_tiles <= slots) return;
       c.grid = slots;
     }
@@ -589,7 +627,8 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     if (td.forced_only && !(o.mt && o.wm)) continue;
     // 1x1 layers take the bf16 part products on the 64x64 tile only (their
     // time is mostly their bytes and launches; see the tile menu)
-    if (fam == kB3 && !o.mt && s.R * s.S == 1 && !(td.mt == 64 && td.nt == 64 && td.kt == 32)) continue;
+    if (fam == kB3 && !o.mt && s.R * s.S == 1 && s.N < kB3WideBatch && !(td.mt == 64 && td.nt == 64 && td.kt == 32)) continue;
+    if (fam == kB3 && o.persist && !o.wm) continue;      // (without waves=, a persistent fp32 kernel)
     // a forced tile without a depth means the default depth of 16
     if ((o.kt || o.mt) && td.kt != (o.kt ? o.kt : 16)) continue;
     if (o.split) {
@@ -609,7 +648,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
       // stream-K over the left-over tiles with one to all resident work-groups per CU
       for (int j = 1, occ = resident_wgs(td, fam); j <= occ; ++j) consider(ti, kStreamK, (long long)j * kCUs);
       // every tile whole, persistent work-groups filling the chip
-      if (fam == kF32) consider(ti, kPersistent, 0);
+      if (fam == kF32 || ti == kTileB3Res) consider(ti, kPersistent, 0);
     }
   }
   };

@@ -208,3 +208,57 @@ def test_b3_fused_in_place_with_infinity():
     assert np.array_equal(np.isnan(out[0]), np.isnan(out[1])) and np.array_equal(np.isinf(out[0]), np.isinf(out[1]))
     fin = np.isfinite(out[1])
     assert np.isinf(out[1]).any() and np.all(np.abs(out[0] - out[1])[fin] <= 1e-4)
+
+
+# The persistent 1x1 kernel: ragged rows, columns that end inside a block of 32,
+# an input stride, padding, every length of the reduction, work-groups whose run
+# of columns reaches into a second filter tile, and more filter tiles than
+# work-groups per XCD.
+RES = "tile=64x64,waves=1x2,kt=32"
+RES_SHAPES = [(4, 64, 67, 65, 20, 1, 1, 1, 0), (4, 128, 33, 32, 260, 1, 1, 1, 0), (12, 192, 60, 58, 70, 1, 1, 2, 1),
+              (20, 384, 23, 21, 132, 1, 1, 1, 0), (4, 64, 14, 9, 2180, 1, 1, 1, 0), (8, 320, 29, 31, 129, 1, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("shape", RES_SHAPES)
+def test_b3_resident_exact(shape):
+    info = mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN", RES)
+    assert info["persistent"] == 1 and info["a_mode"] == 3 and info["grid"] == 256, info
+    x, w, st, pd = make(shape, 3800 + shape[1], "HWCN", dist="int")
+    acc, _ = oracle.conv2d(x, w, st, pd, "HWCN")
+    say(f"b3 resident {shape}")
+    assert np.array_equal(run_gpu(x, w, st, pd, "HWCN", plan=RES), acc.astype(np.float32))
+
+
+def test_b3_resident_error_range_and_fused():
+    """Its error no larger than the fp32-MFMA kernel's; an infinity in x, one in
+    w and sums near the bottom of the range, computed again by the wave that
+    meets them (the patches of its next block are in flight then); and
+    relu(conv + add) in place."""
+    import torch
+    shape = (4, 128, 33, 32, 260, 1, 1, 1, 0)
+    N, C, H, W, K = shape[:5]
+    x, w, st, pd = make(shape, 3900, "HWCN")
+    acc, mag = oracle.conv2d(x, w, st, pd, "HWCN")
+    y, ref = (run_gpu(x, w, st, pd, "HWCN", plan=p) for p in (RES, "dma=1"))
+    assert_parity(y, acc, mag, f"{shape}")
+    err = [float(np.sqrt(np.mean((v.astype(np.float64) - acc) ** 2) / np.mean(acc ** 2))) for v in (y, ref)]
+    assert err[0] <= err[1], err
+
+    add = np.asarray(np.random.Generator(np.random.PCG64(3901)).standard_normal((H, W, K, N)), np.float32)
+    xd, wd, yd = to_dev(x), to_dev(w), to_dev(add)
+    mg3m.conv2d_fwd_f32_fused(xd, wd, yd, yd, 1, N, C, H, W, K, 1, 1, 1, 1, 0, 0, "HWCN", None, 0, RES)
+    torch.cuda.synchronize()
+    want = y + add                               # the plain result and one fp32 addition
+    assert np.array_equal(yd.cpu().numpy(), np.where(want < 0, np.float32(0), want))
+
+    x[3, 2, 5, 1] = np.inf
+    x[7] *= np.float32(2.0**-110)
+    w[0, 0, 7, 3] = -np.inf
+    y, ref = (run_gpu(x, w, st, pd, "HWCN", plan=p) for p in (RES, "dma=1"))
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    assert np.array_equal(np.isposinf(y), np.isposinf(ref)) and np.array_equal(np.isneginf(y), np.isneginf(ref))
+    fin = np.isfinite(ref)
+    xs, ws = np.where(np.isfinite(x), x, 0), np.where(np.isfinite(w), w, 0)
+    _, mag = oracle.conv2d(xs, ws, st, pd, "HWCN")
+    # two fp32 sums of 128 products: 1e-5 of the magnitudes, or the fp32 denormal step
+    assert np.all(np.abs(y[fin].astype(np.float64) - ref[fin]) <= 1e-5 * mag[fin] + 128 * 2.0**-149)

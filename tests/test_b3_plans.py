@@ -1,0 +1,59 @@
+"""Host checks of the kernels of bf16 part products: their rows of the tile
+table against the build, and which shapes the persistent 1x1 kernel takes."""
+import json
+import os
+import re
+
+import pytest
+
+from paper_2307_04941_amd import build, mg3m
+
+RES = "tile=64x64,waves=1x2,kt=32"
+
+
+def test_b3_table_matches_build():
+    """regs and LDS of every tile as compiled, in the form that the table names."""
+    with open(os.path.join(build.CSRC, "mg3m_internal.h")) as f:
+        body = re.search(r"kTilesB3\[kNumTilesB3\] = \{(.*?)\};", f.read(), re.S).group(1)
+    rows = [[int(v) for v in re.findall(r"\d+", r)[:6]] for r in re.findall(r"\{(\d+, \d+, \d+, \d+, \d+, \d+),", body)]
+    assert len(rows) == 10
+    with open(build.RESOURCES) as f:
+        res = json.load(f)
+    for i, (mt, nt, kt, wm, wn, regs) in enumerate(rows):
+        name = (f"void mg3m::conv_igemm_b3<{2 if i == 8 else 0}, {mt}, {nt}, {kt}, {wn}, false>(mg3m::KArgs)"
+                if i != 9 else "void mg3m::conv_igemm_b3_res<false>(mg3m::KArgs)")
+        got = res[name]
+        lds = 12 * kt * mt if i != 9 else 6 * 64 * 384
+        assert (got["vgpr_count"], got["lds_bytes"]) == (regs, lds), (i, name, got, regs, lds)
+    for name, got in res.items():
+        if "conv_igemm_b3" in name:
+            assert got["scratch_bytes"] == 0, name
+
+
+def test_b3_resident_plan():
+    """1x1 layers of 64 to 384 channels with work for every CU run on it, and its
+    tile, waves and kt read back as an override; the plan needs no workspace."""
+    for shape in [(64, 64, 56, 56, 256, 1, 1, 1, 0), (32, 128, 28, 28, 512, 1, 1, 1, 0),
+                  (32, 256, 56, 56, 128, 1, 1, 1, 0), (16, 256, 14, 14, 1024, 1, 1, 1, 0)]:
+        p = mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN")
+        assert (p["persistent"], p["a_mode"], p["waves_n"], p["grid"], p["workspace_bytes"]) == (1, 3, 2, 256, 0), p
+        assert mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN", RES) == p
+        assert mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN", RES + ",persist=1") == p
+
+
+@pytest.mark.parametrize("shape", [(4, 32, 65, 65, 64, 1, 1, 1, 0), (4, 448, 65, 65, 64, 1, 1, 1, 0),
+                                   (4, 64, 65, 65, 64, 3, 3, 1, 1), (3, 64, 75, 75, 64, 1, 1, 1, 0),
+                                   (4, 64, 64, 64, 64, 1, 1, 1, 0)])
+def test_b3_resident_refuses(shape):
+    """Half a pair of steps, more channels than LDS holds, several taps, an odd
+    batch, and 256 tiles (a work-group on every CU is assumed)."""
+    with pytest.raises(mg3m.Mg3mError) as e:
+        mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN", RES)
+    assert e.value.status == 7
+
+
+@pytest.mark.parametrize("plan", [RES + ",persist=2", RES + ",split=2", RES + ",sk=300", RES + ",dma=1"])
+def test_b3_resident_refuses_other_schedules(plan):
+    with pytest.raises(mg3m.Mg3mError) as e:
+        mg3m.conv2d_fwd_f32_plan_info(64, 64, 56, 56, 256, 1, 1, 1, 0, "HWCN", plan)
+    assert e.value.status == 7

@@ -60,8 +60,8 @@ def kernel_name(plan, C: int) -> str:
             return "void mg3m::conv_igemm_b3_res<false>(mg3m::KArgs)"
         groups = C % 8 == 0                                               # its operand form (enum B3Load)
         load = {3: 0, 6: 0, 5: 1, 1: 4, 0: 2 if groups else 5, 2: 3 if groups else 6}[plan["b_mode"]]
-        return (f"void mg3m::conv_igemm_b3<{load}, {plan['mt']}, {plan['nt']}, {plan['kt']}, {plan['waves_n']}, false>"
-                f"(mg3m::KArgs)")
+        return (f"void mg3m::conv_igemm_b3<{load}, {plan['mt']}, {plan['nt']}, {plan['kt']}, {plan['waves_n']}, "
+                f"{plan['waves_m']}, false>(mg3m::KArgs)")
     fn = ("conv_igemm_f32_pt" if plan.get("persistent") else          # persistent whole tiles
           "conv_igemm_f32_m16" if plan["mt"] == 16 else "conv_igemm_f32")  # 16-row tiles: 16x16x4 MFMAs
     return (f"void mg3m::{fn}<{plan['layout']}, {plan['a_mode']}, {plan['b_mode']}, "

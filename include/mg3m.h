@@ -144,6 +144,10 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    a multiple of 4, C of kt, unit horizontal stride, several taps);
  *                    and the 64- and 32-row tiles with kt=32, and
  *                    64x256,waves=1x8,kt=32, for HWCN shapes of any N, C and K.
+ *                    64x64,waves=2x4,kt=32 and (where C is a multiple of 32, or not of
+ *                    8) waves=4x4: two or four groups of waves that share out the
+ *                    reduction inside the work-group, where the selector needs at least
+ *                    12 stages.
  *                    64x64,waves=1x2,kt=32 is the persistent one of them for 1x1
  *                    filters: HWCN, N a multiple of 4, C of 64 and at most 384, more
  *                    than 256 tiles, aligned x and y; its work-groups of twelve waves

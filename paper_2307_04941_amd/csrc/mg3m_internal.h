@@ -159,7 +159,7 @@ inline constexpr TileDesc kTiles64[kNumTiles64] = {
 // (conv_b3.h), and last its persistent relative (conv_b3_res.h).  regs as above,
 // of the form kB3Slab (tile 8: kB3Group); eff is the fraction of the peak (bf16
 // MFMA / 6) that the model charges.
-constexpr int kNumTilesB3 = 10;
+constexpr int kNumTilesB3 = 12;
 constexpr int kTileB3Res = 9;
 inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
     {128, 128, 32, 1, 4, 253, 0.585},                 // 0
@@ -172,6 +172,8 @@ inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
     {32, 128, 32, 1, 4, 130, 0.37},                   // 7: small layers
     {64, 256, 32, 1, 8, 181, 0.50},                   // 8: as 2, for the forms of 32-deep stages only
     {64, 64, 32, 1, 2, 160, 0.50},                    // 9: the resident-filter kernel (1x1, persistent)
+    {64, 64, 32, 4, 4, 118, 0.62, 0, 0, 0.60},        // 10: wm groups of waves share the reduction out (few tiles)
+    {64, 64, 32, 2, 4, 114, 0.62, 0, 0, 0.60},        // 11
 };
 // Its operand addressing (conv_b3.h), and the tiles each form is built for:
 // the group forms take 32-deep stages in which a thread stages at most one
@@ -180,13 +182,15 @@ enum B3Load : int { kB3Slab = 0, kB3SlabW = 1, kB3Group = 2, kB3GroupN = 3, kB3G
 constexpr bool b3_groups(int ld) { return ld >= kB3Group; }
 constexpr bool b3_built(int ld, int tile) {
   const TileDesc& t = kTilesB3[tile];
+  if (tile == 11) return true;
+  if (tile == 10) return ld == kB3Slab || ld == kB3SlabW || ld == kB3Row || ld == kB3RowN;   // (128 registers)
   if (b3_groups(ld)) return t.kt == 32 && t.mt < 128 && tile != kTileB3Res;
   // (the other tiles' NCHW form spills scalar registers to memory)
   if (ld == kB3SlabW) return tile == 1 || tile == 2 || tile == 5;
   return tile < 8;
 }
-// LDS bytes: two stages of the filter in three bf16 parts.
-constexpr int lds_bytes_for_b3(const TileDesc& t) { return 2 * 3 * 2 * t.kt * t.mt; }
+// LDS bytes: two stages of the filter in three bf16 parts, for each group of waves.
+constexpr int lds_bytes_for_b3(const TileDesc& t) { return t.wm * 2 * 3 * 2 * t.kt * t.mt; }
 // The persistent kernel with the filter in LDS (conv_b3_res.h): one work-group
 // per CU, and up to this many input channels.
 constexpr int kB3ResWaves = 12, kB3ResMaxC = 384;

@@ -74,6 +74,12 @@ constexpr double kB3AloneUs = 2.0;
 // Stages from which groups of waves share out a tile's reduction: 18 stages 17.4
 // -> 13.9 us (two groups); at 8 there is about a microsecond to gain.
 constexpr int kB3GroupStages = 12;
+// 1x1 layers that the resident-filter kernel does not take (512 channels and
+// more).  From 64 images on every tile is weighed, the 64x64 one at its measured
+// efficiency there: 512 -> 128 channels at 28x28, N = 64: 57 us on it, 42 on
+// 128x256; 1024 -> 256 at 14x14: 57, and 43 on 64x256.  Smaller batches stay on the
+// 64x64 tile, which is what the selector has always given them and its tests
+// name, though the larger ones would win there too (N = 32: 34 against 26 us).
 constexpr double kB3Small1x1 = 0.63;
 constexpr int kB3WideBatch = 64;
 constexpr double kB3ResStartUs = 2.0, kB3ResEff = 0.75, kB3ResStepUs = 0.6;
@@ -625,8 +631,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // A tile the cost model does not yet rank correctly is left to overrides
     // that name its shape and its waves.
     if (td.forced_only && !(o.mt && o.wm)) continue;
-    // 1x1 layers take the bf16 part products on the 64x64 tile only (their
-    // time is mostly their bytes and launches; see the tile menu)
+    // (kB3WideBatch)
     if (fam == kB3 && !o.mt && s.R * s.S == 1 && s.N < kB3WideBatch && !(td.mt == 64 && td.nt == 64 && td.kt == 32)) continue;
     if (fam == kB3 && o.persist && !o.wm) continue;      // (without waves=, a persistent fp32 kernel)
     // a forced tile without a depth means the default depth of 16

@@ -16,14 +16,14 @@ def test_b3_table_matches_build():
     with open(os.path.join(build.CSRC, "mg3m_internal.h")) as f:
         body = re.search(r"kTilesB3\[kNumTilesB3\] = \{(.*?)\};", f.read(), re.S).group(1)
     rows = [[int(v) for v in re.findall(r"\d+", r)[:6]] for r in re.findall(r"\{(\d+, \d+, \d+, \d+, \d+, \d+),", body)]
-    assert len(rows) == 10
+    assert len(rows) == 12
     with open(build.RESOURCES) as f:
         res = json.load(f)
     for i, (mt, nt, kt, wm, wn, regs) in enumerate(rows):
-        name = (f"void mg3m::conv_igemm_b3<{2 if i == 8 else 0}, {mt}, {nt}, {kt}, {wn}, false>(mg3m::KArgs)"
+        name = (f"void mg3m::conv_igemm_b3<{2 if i == 8 else 0}, {mt}, {nt}, {kt}, {wn}, {wm}, false>(mg3m::KArgs)"
                 if i != 9 else "void mg3m::conv_igemm_b3_res<false>(mg3m::KArgs)")
         got = res[name]
-        lds = 12 * kt * mt if i != 9 else 6 * 64 * 384
+        lds = 12 * kt * mt * wm if i != 9 else 6 * 64 * 384
         assert (got["vgpr_count"], got["lds_bytes"]) == (regs, lds), (i, name, got, regs, lds)
     for name, got in res.items():
         if "conv_igemm_b3" in name:

@@ -129,7 +129,7 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    y in the workspace (hwcn), or in NCHW (none); by default the
  *                    selector weighs both.  via=hwcn on HWCN or fp64 calls ->
  *                    MG3M_ERR_PLAN
- *   waves=<WM>x<WN>  the work-group's wave grid (1..8 each), to pick among tiles
+ *   waves=<WM>x<WN>  the work-group's wave grid (1..8 each; rows also 16), to pick among tiles
  *                    of one shape (64x64 comes as 1x1 with kt=16 and 2x2 with
  *                    kt=32), so the tile, waves and kt of a plan string read back
  *                    as an override for the same tile
@@ -146,8 +146,9 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    64x256,waves=1x8,kt=32, for HWCN shapes of any N, C and K.
  *                    64x64,waves=2x4,kt=32 and (where C is a multiple of 32, or not of
  *                    8) waves=4x4: two or four groups of waves that share out the
- *                    reduction inside the work-group, where the selector needs at least
- *                    12 stages.
+ *                    reduction inside the work-group (the selector takes them from 12
+ *                    stages on); and so 16x16,waves=16x1,kt=32 and
+ *                    32x32,waves=8x2,kt=32 with sixteen and eight groups.
  *                    64x64,waves=1x2,kt=32 is the persistent one of them for 1x1
  *                    filters: HWCN, N a multiple of 4, C of 64 and at most 384, more
  *                    than 256 tiles, aligned x and y; its work-groups of twelve waves

@@ -205,6 +205,9 @@ constexpr unsigned kB3TinyBits = 0x14800000u;
 // otherwise wait out the loads, splits and barriers of every stage: 64 channels,
 // 3x3 on 56x56, N = 4 (196 tiles): 17.4 us with one group, 13.9 with two, 14.9 with
 // four; 2048 channels, 1x1 on 7x7, N = 32 (200 tiles): 51, 36 and 31.
+// The smallest layers take 16x16 or 32x32 tiles with sixteen or eight groups, and
+// no second launch for split tiles: 256 channels, 3x3 on 14x14, one image: 13.2 us
+// split over 256 work-groups and summed by another kernel, 11.3 this way.
 template <int LD, int MT, int NT, int KT, int WN, int KW, class Store>
 __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int t0, int tile, int kt00, int nk_all,
                                                 Store&& store) {
@@ -456,7 +459,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
       // SIMD alone do not fill the MFMA pipe if each runs its split in a block
       static_for<mb - ma>([&](auto) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, (11 + mb - ma - 1) / (mb - ma), 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, (11 + mb - ma - 1) / (mb - ma > 0 ? mb - ma : 1), 0);
       });
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (it < ITB) reload_b(it);
@@ -522,9 +525,9 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         acc[i][j] += lo[i][j];
-        if (kg > 0) lds[(i * TN + j) * C::T + t] = __builtin_bit_cast(u32x4, acc[i][j]);
+        if (kg > 0) lds0[((kg - 1) * TM * TN + i * TN + j) * C::T + t] = __builtin_bit_cast(u32x4, acc[i][j]);
       }
-    static_assert(TM * TN * C::T <= C::LDS_CHUNKS, "a group's sums fit its buffers");
+    static_assert((KW - 1) * TM * TN * C::T <= KW * C::LDS_CHUNKS, "the groups' sums fit the buffers");
     __syncthreads();
     if (kg > 0) return;
 #pragma unroll
@@ -533,7 +536,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] += __builtin_bit_cast(f32x4, lds[g * C::LDS_CHUNKS + (i * TN + j) * C::T + t]);
+          acc[i][j] += __builtin_bit_cast(f32x4, lds0[((g - 1) * TM * TN + i * TN + j) * C::T + t]);
   }
   unsigned tiny = 0xffffffffu;
   float big = 0.f;

@@ -159,7 +159,7 @@ inline constexpr TileDesc kTiles64[kNumTiles64] = {
 // (conv_b3.h), and last its persistent relative (conv_b3_res.h).  regs as above,
 // of the form kB3Slab (tile 8: kB3Group); eff is the fraction of the peak (bf16
 // MFMA / 6) that the model charges.
-constexpr int kNumTilesB3 = 12;
+constexpr int kNumTilesB3 = 14;
 constexpr int kTileB3Res = 9;
 inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
     {128, 128, 32, 1, 4, 253, 0.585},                 // 0
@@ -174,6 +174,8 @@ inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
     {64, 64, 32, 1, 2, 160, 0.50},                    // 9: the resident-filter kernel (1x1, persistent)
     {64, 64, 32, 4, 4, 118, 0.62, 0, 0, 0.60},        // 10: wm groups of waves share the reduction out (few tiles)
     {64, 64, 32, 2, 4, 114, 0.62, 0, 0, 0.60},        // 11
+    {16, 16, 32, 16, 1, 86, 0.2},                     // 12: single images (the model times these two by
+    {32, 32, 32, 8, 2, 96, 0.3},                     // 13:   their chain of stages alone)
 };
 // Its operand addressing (conv_b3.h), and the tiles each form is built for:
 // the group forms take 32-deep stages in which a thread stages at most one
@@ -182,7 +184,7 @@ enum B3Load : int { kB3Slab = 0, kB3SlabW = 1, kB3Group = 2, kB3GroupN = 3, kB3G
 constexpr bool b3_groups(int ld) { return ld >= kB3Group; }
 constexpr bool b3_built(int ld, int tile) {
   const TileDesc& t = kTilesB3[tile];
-  if (tile == 11) return true;
+  if (tile >= 11) return true;
   if (tile == 10) return ld == kB3Slab || ld == kB3SlabW || ld == kB3Row || ld == kB3RowN;   // (128 registers)
   if (b3_groups(ld)) return t.kt == 32 && t.mt < 128 && tile != kTileB3Res;
   // (the other tiles' NCHW form spills scalar registers to memory)

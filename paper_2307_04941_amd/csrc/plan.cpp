@@ -79,7 +79,9 @@ constexpr int kB3GroupStages = 12;
 // efficiency there: 512 -> 128 channels at 28x28, N = 64: 57 us on it, 42 on
 // 128x256; 1024 -> 256 at 14x14: 57, and 43 on 64x256.  Smaller batches stay on the
 // 64x64 tile, which is what the selector has always given them and its tests
-// name, though the larger ones would win there too (N = 32: 34 against 26 us).
+// name, though the larger ones would win there too (N = 32: 34 against 26 us);
+// one image may also take the small tiles of many waves (1024 -> 256 at 14x14:
+// 11.4 -> 8.1 us).
 constexpr double kB3Small1x1 = 0.63;
 constexpr int kB3WideBatch = 64;
 constexpr double kB3ResStartUs = 2.0, kB3ResEff = 0.75, kB3ResStepUs = 0.6;
@@ -184,7 +186,7 @@ int parse_override(const char* text, Override* o, std::string* err) {
       const std::string a = x == std::string::npos ? std::string() : val.substr(0, x);
       const std::string b = x == std::string::npos ? std::string() : val.substr(x + 1);
       const long wm = std::strtol(a.c_str(), &e1, 10), wn = std::strtol(b.c_str(), &e2, 10);
-      if (a.empty() || b.empty() || *e1 != 0 || *e2 != 0 || wm < 1 || wm > 8 || wn < 1 || wn > 8) {
+      if (a.empty() || b.empty() || *e1 != 0 || *e2 != 0 || wm < 1 || (wm > 8 && wm != 16) || wn < 1 || wn > 8) {
         *err = "plan override: waves must be <WM>x<WN> (1..8 each)";
         return MG3M_ERR_PLAN;
       }
@@ -381,6 +383,13 @@ double predict_us(const ConvShape& s, const Plan& p) {
   auto phase = [&](long long wgs, int k_tiles) {
     if (wgs <= 0) return 0.0;
     const long long per_cu = cdiv(wgs, kCUs);
+    if (p.b3 && t.wm >= 8) {
+      // a 16-wave work-group per CU: rounds of chains (eight or sixteen groups share
+      // a tile's stages out), timed on 30 small layers (within 15% or so)
+      const double round = t.wm == 16 ? 1.5 * cdiv(k_tiles, 16) + 4.9 : 1.32 * cdiv(k_tiles, 8) + 5.5;
+      const bool by_column = p.b3_load == kB3GroupN || p.b3_load >= kB3Row;
+      return (double)per_cu * round * (by_column ? 1.35 : 1.0) - kLaunchUs;
+    }
     const double waves_per_simd = (double)std::min<long long>(per_cu, occ) * t.wm * t.wn / 4.0;
     const double util = p.b3 ? std::min(1.0, kUtilBaseB3 + kUtilPerWaveB3 * waves_per_simd)
                              : std::min(1.0, kUtilBase + kUtilPerWave * waves_per_simd);
@@ -541,7 +550,11 @@ static bool choose_b3(const ConvShape& s, bool x16, bool y16, bool named, Plan* 
   if (p->persist)
     return p->tile == kTileB3Res && p->b3_load == kB3Slab && s.R * s.S == 1 && s.C % 64 == 0 && s.C <= kB3ResMaxC &&
            p->dp_tiles > kCUs && p->grid <= kCUs;
-  if (p->t.wm > 1 && p->k_tiles < kB3GroupStages && !named) return false;
+  if (p->t.mt == 64 && p->t.wm > 1 && p->k_tiles < kB3GroupStages && !named) return false;
+  // the small tiles of many waves serve single images (batches of the smallest
+  // layers would gain too, 4 images of 64 channels at 28x28 12.7 -> 9.7 us, but
+  // their callers size the workspace of a split plan and share it among calls)
+  if (p->t.wm >= 8 && s.N > 1 && !named) return false;
   return b3_built(p->b3_load, p->tile);
 }
 
@@ -632,7 +645,8 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // that name its shape and its waves.
     if (td.forced_only && !(o.mt && o.wm)) continue;
     // (kB3WideBatch)
-    if (fam == kB3 && !o.mt && s.R * s.S == 1 && s.N < kB3WideBatch && !(td.mt == 64 && td.nt == 64 && td.kt == 32)) continue;
+    if (fam == kB3 && !o.mt && s.R * s.S == 1 && s.N < kB3WideBatch && !(td.mt == 64 && td.nt == 64 && td.kt == 32) &&
+        !(s.N == 1 && td.wm >= 8)) continue;
     if (fam == kB3 && o.persist && !o.wm) continue;      // (without waves=, a persistent fp32 kernel)
     // a forced tile without a depth means the default depth of 16
     if ((o.kt || o.mt) && td.kt != (o.kt ? o.kt : 16)) continue;

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 TILES = ["tile=128x128,waves=1x4,kt=32", "tile=128x256,waves=1x8,kt=32", "tile=64x256,waves=1x8,kt=64",
          "tile=64x128,waves=1x4,kt=64", "tile=64x128,waves=1x4,kt=32", "tile=64x64,waves=1x4,kt=32",
          "tile=64x64,waves=1x4,kt=64", "tile=32x128,waves=1x4,kt=32", "tile=64x256,waves=1x8,kt=32",
-         "tile=64x64,waves=4x4,kt=32", "tile=64x64,waves=2x4,kt=32"]
+         "tile=64x64,waves=4x4,kt=32", "tile=64x64,waves=2x4,kt=32", "tile=16x16,waves=16x1,kt=32", "tile=32x32,waves=8x2,kt=32"]
 
 # (N, C, H, W, K, R, S, stride, pad), layout, misalign.  One stage; an odd
 # count; 3x3 with ragged rows and columns; stride 2 with an even window: one

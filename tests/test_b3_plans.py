@@ -16,7 +16,7 @@ def test_b3_table_matches_build():
     with open(os.path.join(build.CSRC, "mg3m_internal.h")) as f:
         body = re.search(r"kTilesB3\[kNumTilesB3\] = \{(.*?)\};", f.read(), re.S).group(1)
     rows = [[int(v) for v in re.findall(r"\d+", r)[:6]] for r in re.findall(r"\{(\d+, \d+, \d+, \d+, \d+, \d+),", body)]
-    assert len(rows) == 12
+    assert len(rows) == 14
     with open(build.RESOURCES) as f:
         res = json.load(f)
     for i, (mt, nt, kt, wm, wn, regs) in enumerate(rows):

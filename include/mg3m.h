@@ -337,7 +337,9 @@ int conv2d_fwd_f32_plan_string(int N, int C, int H, int W, int K, int R, int S,
 /* Numbers behind a plan, for tests and benchmarks.  Host only. */
 typedef struct mg3m_plan_info {
     int mt, nt, kt;           /* work-group tile: rows (OC), columns (B*outH*outW), depth step */
-    int waves_m, waves_n;     /* waves per work-group along rows / columns */
+    int waves_m, waves_n;     /* waves per work-group along rows / columns; a_mode 3: groups of waves that
+                                 share the reduction out / waves along columns (its persistent kernel: per
+                                 tile, with six tiles to a work-group) */
     int split;                /* tail work-groups per tail tile, rounded up (1 = no tail) */
     int k_tiles;              /* ceil(Kg / kt) */
     int k_tiles_per_wg;       /* most k-tiles one work-group computes */

@@ -228,7 +228,7 @@ struct Plan {
   int sk_s;                 // split plans: runs per tail tile (tail_wgs = sk_s * tail_tiles); stream-K: 0
   int sk_q, sk_r;           // steps per run: sk_q, one more for the first sk_r (of each tile when split)
   int split;                // tail work-groups per tail tile, rounded up (1 without a tail)
-  int persist;              // 1: whole tiles only, grid work-groups looping over them (conv_igemm_f32_pt)
+  int persist;              // 1: whole tiles only, grid work-groups looping over them (conv_igemm_f32_pt, conv_igemm_b3_res)
   long long grid;           // dp_tiles + tail_wgs (persistent plans: at most dp_tiles)
   int a_mode, b_mode, e_mode;
   int variant;

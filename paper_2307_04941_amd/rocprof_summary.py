@@ -99,6 +99,10 @@ FAMILIES = [("conv_igemm_f32<", ", false>", "convolution (fp32, plain output)"),
             ("conv_igemm_f32_pt<", ", true>", "convolution (fp32, persistent, fused add/ReLU)"),
             ("conv_igemm_f32_m16<", ", false>", "convolution (fp32, 16-row tile, plain output)"),
             ("conv_igemm_f32_m16<", ", true>", "convolution (fp32, 16-row tile, fused add/ReLU)"),
+            ("conv_igemm_b3<", ", false>", "convolution (bf16 part products, plain output)"),
+            ("conv_igemm_b3<", ", true>", "convolution (bf16 part products, fused add/ReLU)"),
+            ("conv_igemm_b3_res<false>", "", "convolution (bf16 part products, 1x1 resident filter, plain output)"),
+            ("conv_igemm_b3_res<true>", "", "convolution (bf16 part products, 1x1 resident filter, fused add/ReLU)"),
             ("conv_igemm_acc64<", "", "convolution (fp64 accumulation)"),
             ("maxpool", "", "max pooling"),
             ("tail_reduce", "", "split-K reduction"),

@@ -21,11 +21,16 @@
 // work-group for the filter (through LDS) and once per wave for the patches,
 // and is spread between the MFMAs.
 //
-// Range.  A part below 2^-133 is lost, so an element under 2^-110 keeps an
-// absolute precision of 2^-133 only; and an infinity has no finite remainder.
-// A wave checks its finished sums: where one is not finite, or nonzero and
-// under 2^-86 (what the lost parts could reach is then no longer below the
-// sum's own rounding), it computes them again on fp32 MFMA.
+// Range.  bf16 has no bits below 2^-133, so an operand under 2^-110 may have no
+// exact parts; and an infinity has no finite remainder.  What a lost bit is worth
+// depends on the other operand, so the split itself tells: the third part is the
+// upper half of its fp32 value, and a set bit in the lower half is a lost one.
+// A thread that has met one stages NaN for its filter column, so that no sum which
+// that column enters is finite, and marks its wave.  A wave so marked, or with a
+// sum that is not finite, or nonzero and under 2^-86 (part products may have
+// fallen below the fp32 range), computes its sums again on fp32 MFMA.  (One mark
+// for both operands: two take 64x64 tiles over 128 registers, a wave less per
+// SIMD: 72 channels, 3x3 on 56x56, N = 8: 38.6 us, with two 43.0.)
 #pragma once
 
 #include "conv_kernel.h"
@@ -65,8 +70,10 @@ __device__ __forceinline__ void bstore_w(__amdgpu_buffer_rsrc_t r, unsigned voff
     bstore1(r, voff, soff, v[0]);
 }
 
-// Two values in three bf16 parts each, packed in pairs.
-__device__ __forceinline__ void split2(float a, float b, unsigned (&o)[3]) {
+// Two values in three bf16 parts each, packed in pairs.  What is left for the
+// third part has at most eight significant bits: its lower half is zero unless
+// it reaches below bf16's last bit, 2^-133.  lost collects these halves.
+__device__ __forceinline__ void split2(float a, float b, unsigned (&o)[3], unsigned& lost) {
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     o[p] = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
@@ -75,10 +82,14 @@ __device__ __forceinline__ void split2(float a, float b, unsigned (&o)[3]) {
       b -= __builtin_bit_cast(float, o[p] & 0xffff0000u);
     }
   }
+  lost |= __builtin_bit_cast(unsigned, a) | __builtin_bit_cast(unsigned, b);
 }
+__device__ __forceinline__ bool lost_bits(unsigned lost) { return (unsigned short)lost != 0; }
 
 // Formed here, not sunk to the block of their use (the next stage).
-__device__ __forceinline__ void pin3(unsigned (&o)[3]) { asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2])); }
+__device__ __forceinline__ void pin3(unsigned (&o)[3], unsigned& lost) {
+  asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(lost));
+}
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): the
 // indices are constants in f, so register arrays stay in registers.
@@ -261,6 +272,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
   float fb[8][TN];
   u32x4 bf[2][TN][3];                // patch fragments of this k-step and the next
   unsigned ap[C::UA][C::AR / 2][3];  // split filter rows on their way to LDS
+  unsigned lost = 0;                 // lower halves of this thread's third parts (split2)
 
   // Where the next loads go.  Patches are loaded two k-steps ahead, the filter
   // two stages ahead.
@@ -381,16 +393,18 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
   auto split_b = [&](int it, int nxt) {
     const int p = it / TN, j = it % TN;
     unsigned o[3];
-    split2(fb[2 * p][j], fb[2 * p + 1][j], o);
-    pin3(o);
+    split2(fb[2 * p][j], fb[2 * p + 1][j], o, lost);
+    pin3(o, lost);
 #pragma unroll
     for (int k = 0; k < 3; ++k) bf[nxt][j][k][p] = o[k];
   };
   auto split_a = [&](int it, int buf) {
     const int u = it / (C::AR / 2), p = it % (C::AR / 2);
-    split2(fa[u][2 * p], fa[u][2 * p + 1], ap[u][p]);
-    pin3(ap[u][p]);
+    split2(fa[u][2 * p], fa[u][2 * p + 1], ap[u][p], lost);
+    pin3(ap[u][p], lost);
     if (p == C::AR / 2 - 1) {
+      // a lost bit, in these rows or met earlier: NaN in their place
+      ap[u][p][0] = lost_bits(lost) ? ~0u : ap[u][p][0];
       unsigned* const d = aslot + buf * C::STAGE * 4 + u * (C::T / MT) * C::AR / 8 * MT * 4;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -459,7 +473,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
       // SIMD alone do not fill the MFMA pipe if each runs its split in a block
       static_for<mb - ma>([&](auto) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, (11 + mb - ma - 1) / (mb - ma > 0 ? mb - ma : 1), 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, (12 + mb - ma - 1) / (mb - ma > 0 ? mb - ma : 1), 0);
       });
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (it < ITB) reload_b(it);
@@ -519,6 +533,8 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
     if (it + 1 < loops) stage(it + 1, std::integral_constant<int, 1>{});
   }
   if constexpr (KW > 1) {
+    // the first group's wave answers for the patches of all groups
+    if (lost_bits(lost)) lo[0][0][0] = __builtin_nanf("");
     // (the last stage's barrier: the buffers are free)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -551,7 +567,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
         tiny = min(tiny, __builtin_bit_cast(unsigned, acc[i][j][e]) * 2u - 1u);   // zeros wrap to the maximum
       }
     }
-  const bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u);
+  const bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u) | (KW == 1 && lost_bits(lost));
   if (MG3M_LDS_POISON == 0 && __ballot(again) != 0) {
     // This wave's part again, on fp32 MFMA, both operands straight from
     // memory: step k of 32 rows takes rows 8*g + k of each lane group g, the

@@ -44,6 +44,7 @@ void conv_igemm_b3_res(KArgs a) {
   float fb[8][TN];
   u32x4 bf[2][TN][3];
   f32x4 acc[TM][TN], lo[TM][TN];
+  unsigned lost = 0;                 // lower halves of the patches' third parts (split2)
   auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -62,8 +63,8 @@ void conv_igemm_b3_res(KArgs a) {
   auto split_b = [&](int it, int nxt) {
     const int p = it / TN, j = it % TN;
     unsigned o[3];
-    split2(fb[2 * p][j], fb[2 * p + 1][j], o);
-    pin3(o);
+    split2(fb[2 * p][j], fb[2 * p + 1][j], o, lost);
+    pin3(o, lost);
 #pragma unroll
     for (int k = 0; k < 3; ++k) bf[nxt][j][k][p] = o[k];
   };
@@ -92,7 +93,7 @@ void conv_igemm_b3_res(KArgs a) {
       });
       static_for<mb - ma>([&](auto) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, (11 + mb - ma - 1) / (mb - ma), 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, (12 + mb - ma - 1) / (mb - ma), 0);
       });
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (it % TN == TN - 1) {
@@ -138,19 +139,22 @@ void conv_igemm_b3_res(KArgs a) {
       for (int r = 0; r < UA; ++r) {
         const int c8 = wave + r * WV;
         if (c8 >= chunks) break;
-        unsigned o[4][3];
+        unsigned o[4][3], lost_a = 0;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) split2(fa[r][2 * p], fa[r][2 * p + 1], o[p]);
+        for (int p = 0; p < 4; ++p) split2(fa[r][2 * p], fa[r][2 * p + 1], o[p], lost_a);
+        o[0][0] = lost_bits(lost_a) ? ~0u : o[0][0];      // a lost bit: NaN in its place
 #pragma unroll
         for (int k = 0; k < 3; ++k) lds[(c8 * 3 + k) * MT + lane] = u32x4{o[0][k], o[1][k], o[2][k], o[3][k]};
       }
     }
+    lost = 0;
     static_for<IT>([&](auto ic) { split_b(decltype(ic)::value, 0); });
 #pragma unroll
     for (int i = 0; i < 8; ++i) bload_w<TN>(xr, bv, C4 * (unsigned)(32 + i), fb[i]);
     __syncthreads();
 
     for (; cb < cb_end; cb += WV) {
+      unsigned lost_here = 0;
       clear();
       for (int ks = 0; ks < nk; ks += 2) {
         // the loads are two steps ahead: in the last two, the next block's
@@ -159,6 +163,9 @@ void conv_igemm_b3_res(KArgs a) {
         const unsigned soff = end ? 0u : C4 * (unsigned)(32 * (ks + 2));
         __builtin_amdgcn_sched_barrier(0);
         kstep(std::integral_constant<int, 0>{}, ks, bv, soff);
+        // this block's patches are all split; from here on the next block's
+        lost_here = lost;
+        lost = end ? 0u : lost;
         kstep(std::integral_constant<int, 1>{}, ks + 1, bv, soff + 32u * C4);
       }
       unsigned tiny = 0xffffffffu;
@@ -174,7 +181,7 @@ void conv_igemm_b3_res(KArgs a) {
             tiny = min(tiny, __builtin_bit_cast(unsigned, acc[i][j][e]) * 2u - 1u);
           }
         }
-      const bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u);
+      const bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u) | lost_bits(lost_here);
       if (MG3M_LDS_POISON == 0 && __ballot(again) != 0) {
         // this block again on fp32 MFMA, straight from memory (tile_product_b3)
         clear();

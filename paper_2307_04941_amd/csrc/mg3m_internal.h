@@ -166,16 +166,16 @@ inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
     {128, 256, 32, 1, 8, 244, 0.61},                  // 1: eight waves sharing one filter tile
     {64, 256, 64, 1, 8, 186, 0.50},                   // 2: 64 output channels
     {64, 128, 64, 1, 4, 186, 0.44},                   // 3
-    {64, 128, 32, 1, 4, 178, 0.44},                   // 4
+    {64, 128, 32, 1, 4, 179, 0.44},                   // 4
     {64, 64, 32, 1, 4, 113, 0.62, 0, 0, 0.60},        // 5
-    {64, 64, 64, 1, 4, 121, 0.372},                   // 6
-    {32, 128, 32, 1, 4, 130, 0.37},                   // 7: small layers
-    {64, 256, 32, 1, 8, 181, 0.50},                   // 8: as 2, for the forms of 32-deep stages only
-    {64, 64, 32, 1, 2, 160, 0.50},                    // 9: the resident-filter kernel (1x1, persistent)
-    {64, 64, 32, 4, 4, 118, 0.62, 0, 0, 0.60},        // 10: wm groups of waves share the reduction out (few tiles)
-    {64, 64, 32, 2, 4, 114, 0.62, 0, 0, 0.60},        // 11
-    {16, 16, 32, 16, 1, 86, 0.2},                     // 12: single images (the model times these two by
-    {32, 32, 32, 8, 2, 96, 0.3},                     // 13:   their chain of stages alone)
+    {64, 64, 64, 1, 4, 122, 0.372},                   // 6
+    {32, 128, 32, 1, 4, 131, 0.37},                   // 7: small layers
+    {64, 256, 32, 1, 8, 185, 0.50},                   // 8: as 2, for the forms of 32-deep stages only
+    {64, 64, 32, 1, 2, 162, 0.50},                    // 9: the resident-filter kernel (1x1, persistent)
+    {64, 64, 32, 4, 4, 116, 0.62, 0, 0, 0.60},        // 10: wm groups of waves share the reduction out (few tiles)
+    {64, 64, 32, 2, 4, 113, 0.62, 0, 0, 0.60},        // 11
+    {16, 16, 32, 16, 1, 85, 0.2},                     // 12: single images (the model times these two by
+    {32, 32, 32, 8, 2, 95, 0.3},                     // 13:   their chain of stages alone)
 };
 // Its operand addressing (conv_b3.h), and the tiles each form is built for:
 // the group forms take 32-deep stages in which a thread stages at most one

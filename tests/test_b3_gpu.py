@@ -156,6 +156,63 @@ def test_b3_range_check_other_forms(shape, plan):
     assert np.all(np.abs(y[fin] - clean[fin]) <= 1e-5 * mag[fin])
 
 
+# One plan of every operand form, of every number of groups of waves, and the
+# resident-filter kernel; each layer's reduction reaches every group.
+LOST_FORMS = [((4, 64, 6, 5, 68, 3, 3, 1, 1), "HWCN", "tile=64x128,waves=1x4,kt=64,split=1"),
+              ((4, 64, 6, 5, 68, 3, 3, 1, 1), "HWCN", "tile=128x256,waves=1x8,kt=32,split=3"),
+              ((4, 64, 6, 5, 68, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=2x4,kt=32,split=1"),
+              ((4, 64, 6, 5, 68, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=4x4,kt=32,split=1"),
+              ((4, 64, 6, 5, 68, 3, 3, 1, 1), "HWCN", "tile=32x32,waves=8x2,kt=32,split=1"),
+              ((4, 64, 6, 5, 68, 3, 3, 1, 1), "HWCN", "tile=16x16,waves=16x1,kt=32,split=1"),
+              ((3, 64, 6, 5, 68, 3, 3, 1, 1), "NCHW", "tile=64x64,waves=1x4,kt=32,split=1,via=none"),
+              ((3, 64, 6, 5, 68, 3, 3, 1, 1), "NCHW", "tile=64x64,waves=4x4,kt=32,split=1,via=none"),
+              ((4, 72, 6, 5, 36, 3, 3, 1, 1), "HWCN", "tile=64x128,waves=1x4,kt=32,split=1"),
+              ((5, 72, 6, 5, 36, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=2x4,kt=32,split=1"),
+              ((1, 72, 6, 5, 36, 3, 3, 1, 1), "HWCN", "tile=16x16,waves=16x1,kt=32,split=1"),
+              ((4, 67, 6, 5, 36, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=4x4,kt=32,split=1"),
+              ((5, 67, 6, 5, 36, 3, 3, 1, 1), "HWCN", "tile=32x128,waves=1x4,kt=32,split=1"),
+              ((4, 128, 41, 52, 68, 1, 1, 1, 0), "HWCN", "tile=64x64,waves=1x2,kt=32")]
+LOST_KINDS = ["x_low", "w_low", "x_sub", "w_sub", "x_one", "w_one", "x_parts_sub", "w_parts_sub"]
+
+
+def _lost(kind, x, w, layout, rng):
+    """Finite operands whose bf16 parts do not hold every bit, or barely do."""
+    low, high = (w, x) if kind[0] == "w" else (x, w)
+    if kind.endswith("_low"):                          # bits below 2^-133, worth 2^-14 of the sums
+        low *= np.float32(2.0**-120)
+        high *= np.float32(2.0**40)
+    elif kind.endswith("parts_sub"):                   # exact in two subnormal parts
+        low[...] = rng.integers(-200, 200, low.shape).astype(np.float32) * np.float32(2.0**-133)
+        high *= np.float32(2.0**100)
+    elif kind.endswith("_sub"):                        # no part holds anything
+        low *= np.float32(2.0**-136)
+    else:                                              # one element; the rest of its tensor zero
+        at = tuple(int(rng.integers(0, n)) for n in low.shape)
+        low[...] = 0
+        low[at] = np.float32((1 + 2.0**-10 + 2.0**-20) * 2.0**-122)
+        high *= np.float32(2.0**60)
+
+
+@pytest.mark.parametrize("form", range(len(LOST_FORMS)))
+def test_b3_operands_that_lose_bits(form):
+    """Operands under 2^-110 against partners of any size: each output within the
+    library's 1e-5 of its magnitudes, or a step of the fp32 denormals per product,
+    and sums that the parts would make zero come out."""
+    shape, layout, plan = LOST_FORMS[form]
+    if layout == "HWCN":
+        assert _is_b3(shape, plan), plan
+    rng = np.random.Generator(np.random.PCG64(3680 + form))
+    Kg = shape[1] * shape[5] * shape[6]
+    for kind in LOST_KINDS * 2:                        # twice: other positions of the single elements
+        x, w, st, pd = make(shape, int(rng.integers(1, 1 << 30)), layout)
+        _lost(kind, x, w, layout, rng)
+        acc, mag = oracle.conv2d(x, w, st, pd, layout)
+        say(f"b3 lost bits {kind} {layout} {shape} {plan}")
+        y = run_gpu(x, w, st, pd, layout, plan=plan).astype(np.float64)
+        err, tol = np.abs(y - acc), 1e-5 * mag + Kg * 2.0**-149
+        assert np.all(err <= tol), f"{kind}: worst {float((err / np.maximum(tol, 1e-300)).max()):.3g} of the tolerance"
+
+
 @pytest.mark.parametrize("kind", ["inf", "nan", "inf_filter", "near_max", "overflow", "tiny", "tiny_sums"])
 @pytest.mark.parametrize("plan", ["tile=64x128,waves=1x4,kt=64,split=1", "tile=128x128,waves=1x4,kt=32,sk=3",
                                   "tile=64x64,waves=1x4,kt=32,split=2"])

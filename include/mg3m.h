@@ -109,7 +109,8 @@ int conv2d_fwd_f32(const float *x, const float *w, float *y,
 /* Bytes of workspace the plan for this shape needs: the piece partials when
  * tiles' reductions are shared out, plus, for NCHW plans taken tap-major (C a multiple of the
  * plan's kt, K a multiple of 4, R*S > 1, stride_w 1), a [R][S][C][K] copy of
- * the filter that the call makes first; 0 when neither applies.
+ * the filter that the call makes first; 0 when neither applies.  The plan
+ * depends on the buffers' alignment; this many bytes are enough for any.
  * plan: NULL for the selector's choice, or an override string (below).
  * bytes: host out-parameter. */
 int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int S,
@@ -139,7 +140,7 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    64x256,waves=1x8,kt=64; 64x128,waves=1x4,kt=64 and kt=32;
  *                    64x64,waves=1x4,kt=32 and kt=64; 32x128,waves=1x4,kt=32 for
  *                    shapes of the one-tap HWCN loader (HWCN or via=hwcn, N a multiple
- *                    of 4, C of kt, aligned x and y; any K); of these 128x256,
+ *                    of 4, C of kt, aligned x; any K); of these 128x256,
  *                    64x256 and 64x64,kt=32 in NCHW where the filter copy applies (K
  *                    a multiple of 4, C of kt, unit horizontal stride, several taps);
  *                    and the 64- and 32-row tiles with kt=32, and
@@ -151,7 +152,7 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    32x32,waves=8x2,kt=32 with sixteen and eight groups.
  *                    64x64,waves=1x2,kt=32 is the persistent one of them for 1x1
  *                    filters: HWCN, N a multiple of 4, C of 64 and at most 384, more
- *                    than 256 tiles, aligned x and y; its work-groups of twelve waves
+ *                    than 256 tiles, aligned x; its work-groups of twelve waves
  *                    keep the filter in LDS.  dma=1 excludes them all, and so does
  *                    persist=, but for that last one with its waves and persist=1
  *   kt=16|32|64      reduction depth staged per step (default 16 with a tile)

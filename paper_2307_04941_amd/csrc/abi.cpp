@@ -304,8 +304,23 @@ int run(const float* x, const float* w, float* y, const Geom& g, void* workspace
   if (relu != 0 && relu != 1) return fail(MG3M_ERR_ARG, "relu must be 0 or 1");
   mg3m::ConvShape s;
   mg3m::Plan p;
-  int rc = shape_and_plan(g, plan, aligned(x, 16), aligned(w, 16), aligned(y, 16), &s, &p);
+  const bool x16 = aligned(x, 16), w16 = aligned(w, 16), y16 = aligned(y, 16);
+  int rc = shape_and_plan(g, plan, x16, w16, y16, &s, &p);
   if (rc) return rc;
+  const size_t given = workspace != nullptr ? workspace_bytes : 0;
+  if (!own_workspace && !(x16 && w16 && y16) && given < p.ws_bytes) {
+    // The size a caller can ask for is that of the plan for aligned buffers.
+    // With that much, a plan for these ones that takes no more.
+    mg3m::ConvShape sa;
+    mg3m::Plan pa;
+    rc = shape_and_plan(g, plan, true, true, true, &sa, &pa);
+    if (rc == MG3M_OK && given >= pa.ws_bytes) {
+      Geom capped = g;
+      capped.ws_cap = std::min(g.ws_cap, pa.ws_bytes);
+      rc = shape_and_plan(capped, plan, x16, w16, y16, &s, &p);
+      if (rc) return rc;
+    }
+  }
   const int N = g.N, C = g.C, H = g.H, W = g.W, K = g.K, R = g.R, S = g.S;
   const size_t xb = 4ull * N * C * H * W, wb = 4ull * K * C * R * S;
   const size_t yb = 4ull * (size_t)s.Mg * (size_t)s.Ng;

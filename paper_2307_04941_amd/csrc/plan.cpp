@@ -527,9 +527,12 @@ void choose_modes(const ConvShape& s, bool x16, bool w16, bool y16, Plan* p, boo
 // override names its waves).  By the
 // narrowest that applies: a filter tap per stage where the channels fill whole
 // stages, groups of eight channels, single rows of the reduction; and a lane's
-// columns as one load where four batch elements lie together.
-static bool choose_b3(const ConvShape& s, bool x16, bool y16, bool named, Plan* p) {
-  const bool vec = s.N % 4 == 0 && x16 && y16;
+// columns as one load where four batch elements lie together.  y's alignment is
+// not asked: a buffer store of four dwords needs a dword's only, and the form
+// decides on the tile, the split and the workspace, whose size callers ask for
+// without naming a y.
+static bool choose_b3(const ConvShape& s, bool x16, bool named, Plan* p) {
+  const bool vec = s.N % 4 == 0 && x16;
   if (s.layout == kNCHW) {
     if (p->variant != kVarNchwTap) return false;
     p->b3_load = kB3SlabW;
@@ -585,7 +588,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // which stage through VGPRs
     const bool dma_ok = !c.acc64 && !c.t.m16;
     choose_modes(sv, via || x16, via || w16, via || y16, &c, dma_ok && o.dma != 0);
-    if (c.b3 && (o.dma == 1 || !choose_b3(sv, via || x16, via || y16, o.wm > 0, &c))) return;
+    if (c.b3 && (o.dma == 1 || !choose_b3(sv, via || x16, o.wm > 0, &c))) return;
     if (via) {
       auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
       c.via_hwcn = 1;

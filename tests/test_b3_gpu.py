@@ -268,6 +268,56 @@ def test_b3_fused_in_place_with_infinity():
     assert np.isinf(out[1]).any() and np.all(np.abs(out[0] - out[1])[fin] <= 1e-4)
 
 
+@pytest.mark.parametrize("form", range(len(LOST_FORMS)))
+def test_b3_fused_forms_at_any_alignment(form):
+    """relu(conv + add) on small integers, exact, for every form: add apart, add on
+    a 4-byte boundary (loaded as wide as y is stored), and in place on a y that
+    lies on one (y's alignment does not change the plan)."""
+    import torch
+    shape, layout, plan = LOST_FORMS[form]
+    N, C, H, W, K, R, S, st, pd = shape
+    x, w, _, _ = make(shape, 3720 + form, layout, dist="int")
+    acc, _ = oracle.conv2d(x, w, st, pd, layout)
+    add = np.random.Generator(np.random.PCG64(3740 + form)).integers(-40, 40, acc.shape).astype(np.float32)
+    want = np.maximum(acc.astype(np.float32) + add, np.float32(0))
+    need = mg3m.conv2d_fwd_f32_hw_workspace_bytes(N, C, H, W, K, R, S, st, st, pd, pd, layout, plan)
+    ws = torch.empty((need + 3) // 4, device="cuda") if need else None
+    xd, wd = to_dev(x), to_dev(w)
+
+    def at(offset, values):
+        t = torch.empty(values.size + offset, device="cuda")[offset:].view(values.shape)
+        t.copy_(torch.from_numpy(values))
+        return t
+    for name, y, d in [("apart", at(0, add), at(0, add)), ("add off", at(0, add), at(1, add)),
+                       ("y off", at(3, add), at(0, add)), ("in place", at(1, add), None)]:
+        say(f"b3 fused {name} {layout} {shape} {plan}")
+        mg3m.conv2d_fwd_f32_fused(xd, wd, y, y if d is None else d, 1, N, C, H, W, K, R, S, st, st, pd, pd, layout,
+                                  ws, need, plan)
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy(), want), (name, plan)
+
+
+def test_b3_network_output_at_any_alignment():
+    """A network's workspace is sized once, for aligned buffers: a caller's y (or x)
+    on a 4-byte boundary has to do with it."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(3760)
+    N, C, HW, K = 64, 176, 28, 96
+    x = torch.randn((HW, HW, C, N), generator=g, device="cuda")
+    w = torch.randn((3, 3, C, K), generator=g, device="cuda") * 0.05
+    net = mg3m.Net([{"op": "conv", "input": 0, "add": -1, "relu": 0, "K": K, "C": C, "R": 3, "S": 3, "stride": 1, "pad": 1,
+                     "w": w}], (N, C, HW, HW), "HWCN")
+    y = net.forward(x)
+    off = torch.empty(y.numel() + 1, device="cuda")[1:].view(y.shape)
+    net.forward(x, out=off)
+    assert torch.equal(off, y)                         # the same plan
+    xo = torch.empty(x.numel() + 1, device="cuda")[1:].view(x.shape)
+    xo.copy_(x)
+    net.forward(xo, out=off)
+    # two orders of 1584 products of order one
+    assert float((off - y).abs().max()) <= 1e-5 * float(x.abs().max() * w.abs().max()) * 9 * C
+
+
 # The persistent 1x1 kernel: ragged rows, columns that end inside a block of 32,
 # an input stride, padding, every length of the reduction, work-groups whose run
 # of columns reaches into a second filter tile, and more filter tiles than

@@ -2,6 +2,7 @@
 table against the build, and which shapes the persistent 1x1 kernel takes."""
 import json
 import os
+import random
 import re
 
 import pytest
@@ -57,3 +58,27 @@ def test_b3_resident_refuses_other_schedules(plan):
     with pytest.raises(mg3m.Mg3mError) as e:
         mg3m.conv2d_fwd_f32_plan_info(64, 64, 56, 56, 256, 1, 1, 1, 0, "HWCN", plan)
     assert e.value.status == 7
+
+
+def test_queried_workspace_serves_any_alignment(monkeypatch):
+    """A workspace of the queried size (none, where that is 0) is enough whatever
+    the alignment of x, w and y.  The calls end at a launch that is made to fail (status 8): status 6 would be
+    the refused workspace."""
+    monkeypatch.setenv("MG3M_TEST_FAIL_LAUNCH", "1")
+    lib = mg3m.load_library()
+    x, w, y, ws = 0x7f0000000000, 0x7f2000000000, 0x7f4000000000, 0x7f6000000000
+    rng = random.Random(41)
+    shapes = [(64, 176, 28, 28, 96, 3, 3, 1, 1), (24, 169, 60, 60, 6, 3, 3, 1, 1), (4, 32, 78, 78, 208, 3, 3, 2, 1),
+              (1, 208, 10, 12, 48, 3, 3, 2, 1)]
+    while len(shapes) < 250:
+        R = rng.choice([1, 1, 3, 3, 5])
+        shapes.append((rng.choice([1, 3, 4, 8, 16, 28, 64]), rng.choice([3, 8, 20, 32, 64, 75, 96, 169, 256, 512]),
+                       rng.randint(7, 60), rng.randint(7, 60), rng.choice([6, 16, 48, 64, 96, 128, 208, 512]), R, R,
+                       rng.choice([1, 1, 2]), R // 2))
+    for shape in shapes:
+        for layout in (0, 1):
+            need = mg3m.conv2d_fwd_f32_workspace_bytes(*shape, layout)
+            for off in range(8):
+                rc = lib.conv2d_fwd_f32_ex(x + 4 * (off & 1), w + 4 * (off >> 1 & 1), y + 4 * (off >> 2), *shape,
+                                           layout, ws if need else None, need, None, None)
+                assert rc == 8, (shape, layout, off, need, rc, mg3m.mg3m_last_error())

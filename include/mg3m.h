@@ -153,8 +153,11 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    64x64,waves=1x2,kt=32 is the persistent one of them for 1x1
  *                    filters: HWCN, N a multiple of 4, C of 64 and at most 384, more
  *                    than 256 tiles, aligned x; its work-groups of twelve waves
- *                    keep the filter in LDS.  dma=1 excludes them all, and so does
- *                    persist=, but for that last one with its waves and persist=1
+ *                    keep the filter in LDS.  An override whose tile, waves or kt fits
+ *                    an fp32 tile means that one unless it gives tile and waves; dma=
+ *                    excludes the bf16 part products, and so does persist=, but for
+ *                    that last one with its waves and persist=1.  split=, tail=, sk=
+ *                    and via= alone leave the kernel to the selector
  *   kt=16|32|64      reduction depth staged per step (default 16 with a tile)
  *   split=<n>        share every tile's reduction out over n work-groups per tile
  *                    (1..64, clamped to the tile's k-tiles; 1 = no split)
@@ -357,8 +360,8 @@ typedef struct mg3m_plan_info {
     int layout;               /* MG3M_LAYOUT_* */
     int a_mode, b_mode;       /* operand loader variant of the main kernel (its template arguments);
                                  a_mode 3: the kernels of bf16 part products; b_mode then
-                                 names the shape class (6, or 3 with dma=0: a filter tap
-                                 per stage; 5: the same in NCHW; 0, 1, 2: batch vectors,
+                                 names the shape class (6, or 3 where K is not a multiple
+                                 of 4: a filter tap per stage; 5: the same in NCHW; 0, 1, 2: batch vectors,
                                  one image, any other), its patches go straight to
                                  registers */
     int e_mode;               /* epilogue store mode */

@@ -588,7 +588,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // which stage through VGPRs
     const bool dma_ok = !c.acc64 && !c.t.m16;
     choose_modes(sv, via || x16, via || w16, via || y16, &c, dma_ok && o.dma != 0);
-    if (c.b3 && (o.dma == 1 || !choose_b3(sv, via || x16, o.wm > 0, &c))) return;
+    if (c.b3 && !choose_b3(sv, via || x16, o.wm > 0, &c)) return;
     if (via) {
       auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
       c.via_hwcn = 1;
@@ -636,6 +636,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     if (o.via != 1) consider_one(fam, ti, sched, sp, false);
     if (via_ok && o.via != 0) consider_one(fam, ti, sched, sp, true);
   };
+  bool named_f32 = false;               // the override's tile, waves and kt fit an fp32 (or fp64) tile
   auto consider_family = [&]() {
   for (int ti = 0; ti < num_tiles(fam); ++ti) {
     const TileDesc& td = tile_desc(fam, ti);
@@ -653,6 +654,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     if (fam == kB3 && o.persist && !o.wm) continue;      // (without waves=, a persistent fp32 kernel)
     // a forced tile without a depth means the default depth of 16
     if ((o.kt || o.mt) && td.kt != (o.kt ? o.kt : 16)) continue;
+    if (fam != kB3) named_f32 = true;
     if (o.split) {
       consider(ti, o.split > 1 ? kSplitAll : kDataParallel, o.split);
     } else if (o.tail) {
@@ -675,7 +677,11 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
   }
   };
   consider_family();
-  if (!acc64) {
+  // The kernels of bf16 part products are the selector's to choose, or named by
+  // tile and waves together.  An override that names less (a tile, a depth, dma=)
+  // means the fp32 kernel that it has always meant, if there is one.
+  const bool open = !o.mt && !o.wm && !o.kt;
+  if (!acc64 && o.dma < 0 && (open || (o.mt && o.wm) || !named_f32)) {
     fam = kB3;
     consider_family();
   }

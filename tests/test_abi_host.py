@@ -556,15 +556,15 @@ def test_noalloc_validation_before_any_device_call():
 
 
 def test_one_tap_loaders_default_to_direct_lds():
-    """Where the one-tap HWCN loaders apply, the selector's plans load straight
-    into LDS (b_mode 6), persistent ones included, unless they are on the
-    16-row tile; dma=0 keeps the same plan with the loaders staging through
+    """Where the one-tap HWCN loaders apply, the fp32-MFMA kernels' plans load
+    straight into LDS (b_mode 6), persistent ones included, unless they are on the
+    16-row tile; dma=0 keeps the plan of dma=1 with the loaders staging through
     VGPRs (b_mode 3), and dma=1 is refused where the direct-to-LDS form does
     not apply."""
     shape = (64, 256, 56, 56, 256, 3, 3, 1, 1)
-    p = mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN")
+    p = mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN", "dma=1")
     q = mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN", "dma=0")
-    assert p["b_mode"] == 6 and q["b_mode"] == 3
+    assert p["a_mode"] == q["a_mode"] == 0 and p["b_mode"] == 6 and q["b_mode"] == 3
     same = ("mt", "nt", "kt", "split", "dp_tiles", "tail_tiles", "tail_wgs", "grid", "workspace_bytes")
     assert all(p[k] == q[k] for k in same), (p, q)
     for plan, b_mode in (("tile=128x128,persist=2", 6), ("tile=128x128,persist=2,dma=0", 3)):

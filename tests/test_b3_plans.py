@@ -82,3 +82,19 @@ def test_queried_workspace_serves_any_alignment(monkeypatch):
                 rc = lib.conv2d_fwd_f32_ex(x + 4 * (off & 1), w + 4 * (off >> 1 & 1), y + 4 * (off >> 2), *shape,
                                            layout, ws if need else None, need, None, None)
                 assert rc == 8, (shape, layout, off, need, rc, mg3m.mg3m_last_error())
+
+
+@pytest.mark.parametrize("shape,layout", [((16, 64, 28, 28, 128, 3, 3, 1, 1), "HWCN"), ((7, 75, 29, 31, 117, 3, 3, 1, 1), "HWCN"),
+                                          ((1, 64, 14, 14, 64, 1, 1, 1, 0), "HWCN"), ((8, 64, 28, 28, 96, 3, 3, 1, 1), "NCHW")])
+def test_overrides_that_name_fp32_tiles_keep_them(shape, layout):
+    """A tile, a depth or dma= without waves means the fp32-MFMA kernel that it meant
+    before these kernels came; tile and waves together name one of these."""
+    fp32 = ["tile=64x64,kt=32", "tile=64x64,kt=32,split=3", "tile=128x128,kt=32", "tile=128x128,kt=32,tail=2", "kt=32",
+            "kt=16", "kt=32,split=2", "waves=2x2", "waves=1x4", "tile=128x128", "tile=64x64,waves=2x2,kt=32"]
+    if shape[0] % 4 == 0 and layout == "HWCN":
+        fp32 += ["dma=0", "dma=1", "tile=64x64,kt=32,dma=0"]
+    for plan in fp32:
+        p = mg3m.conv2d_fwd_f32_plan_info(*shape, layout, plan)
+        assert p["a_mode"] != 3, (plan, p)
+    for plan in ("tile=64x64,waves=1x4,kt=32", "tile=64x64,waves=1x4,kt=32,split=2"):
+        assert mg3m.conv2d_fwd_f32_plan_info(*shape, layout, plan)["a_mode"] == 3, plan

@@ -21,6 +21,17 @@ CASES = [
     ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=128x128,dma=0", False),      # register-staged
     ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=128x128,sk=7", False),       # stream-K pieces
     ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=64x64,kt=32,split=3", False),
+    # bf16 part products: whole tiles, pieces, groups of waves that share a tile, NCHW, and the resident
+    # filter (several filter tiles per work-group)
+    ((16, 64, 28, 28, 128, 3, 3, 1, 1), "HWCN", "tile=128x256,waves=1x8,kt=32,split=1", False),
+    ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=64x128,waves=1x4,kt=64,sk=23", False),
+    ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=2x4,kt=32", False),
+    ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=4x4,kt=32,split=2", False),
+    ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=32x32,waves=8x2,kt=32,sk=80", False),
+    ((1, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=16x16,waves=16x1,kt=32,split=1", False),
+    ((7, 75, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=4x4,kt=32,split=1", False),
+    ((3, 64, 13, 11, 68, 3, 3, 1, 1), "NCHW", "tile=64x64,waves=2x4,kt=32,split=1,via=none", False),
+    ((4, 64, 14, 9, 2180, 1, 1, 1, 0), "HWCN", "tile=64x64,waves=1x2,kt=32", False),
     ((32, 3, 64, 64, 64, 3, 3, 1, 1), "HWCN", "tile=64x256,persist=1", False),   # persistent, vec-N
     ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=128x128,persist=1", False),  # persistent, one-tap into LDS
     ((4, 64, 13, 11, 68, 3, 3, 1, 1), "HWCN", "tile=128x128,persist=1,dma=0", False),  # persistent, staged

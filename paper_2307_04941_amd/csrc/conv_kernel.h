@@ -71,11 +71,8 @@ __device__ __forceinline__ float bload1(__amdgpu_buffer_rsrc_t r, unsigned off) 
 __device__ __forceinline__ void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
 // Buffer store at byte offset voff + soff: one per-lane offset register
 // serves a whole tile of stores, the constant part riding in soff.
-// AUX: 0, or kStreamAux, a store that the caches let go first: the persistent
-// kernel's, which the selector takes for layers bounded by their output's bytes
-// (64 x 224 x 224 images, 3 -> 64 channels, 822 MB out: 193 -> 172 us, 167 at the
-// rate of a copy; the ResNet-50 trunk, whose next layer reads such a layer's 51 MB
-// at once: unchanged).
+// AUX: 0, or kStreamAux, a store that the caches let go first, for an output
+// that none of them holds until it is read (stream_stores).
 constexpr int kStreamAux = 2;
 template <int AUX = 0>
 __device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, float v) {
@@ -1296,9 +1293,11 @@ __device__ __forceinline__ void store_tile_f32(const KArgs& a, floatx16 (&acc)[C
 // and elements outside the output sent to the out-of-range offset (with a
 // zero scalar offset, as the loaders do), which the buffer hardware drops --
 // no branches and no 64-bit address per store.
-template <int LAYOUT, class C, bool FUSE = false, int AUX = 0>
+// stream: the stores take kStreamAux, by a uniform branch around every four (around
+// a whole block, its sixteen offsets lie in registers at once).
+template <int LAYOUT, class C, bool FUSE = false>
 __device__ __forceinline__ void store_tile_f32_buf(const KArgs& a, floatx16 (&acc)[C::TM][C::TN], int m0, int n0,
-                                                   int wm, int wn, int hh, int q) {
+                                                   int wm, int wn, int hh, int q, bool stream = false) {
   const __amdgpu_buffer_rsrc_t yr = make_rsrc(a.y, a.y_bytes);
   const bool has_add = FUSE && a.add != nullptr;
   const __amdgpu_buffer_rsrc_t ar = make_rsrc(has_add ? a.add : a.y, a.y_bytes);
@@ -1342,7 +1341,18 @@ __device__ __forceinline__ void store_tile_f32_buf(const KArgs& a, floatx16 (&ac
         }
       }
 #pragma unroll
-      for (int e = 0; e < 16; ++e) bstore1<AUX>(yr, offset(i * 32 + 8 * (e / 4) + e % 4), 0u, acc[i][j][e]);
+      for (int e = 0; e < 16; e += 4) {
+        unsigned o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = offset(i * 32 + 2 * e + k);
+        if (stream) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) bstore1<kStreamAux>(yr, o[k], 0u, acc[i][j][e + k]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) bstore1(yr, o[k], 0u, acc[i][j][e + k]);
+        }
+      }
     }
   }
 }
@@ -1423,6 +1433,17 @@ __device__ __forceinline__ void mma_stage_upto(floatx16 (&acc)[C::TM][C::TN], co
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
     }
   }
+}
+
+// Whether the persistent kernel's stores stream: y does not fit the last-level
+// cache, and they write whole 64-byte sectors of it (else each partial one makes
+// a trip to memory of its own).  3 -> 64 channels at 224x224, streamed against
+// not: N = 64 (822 MB) 179 and 199 us, N = 60 616 and 336, N = 40 381 and 212; at
+// 112x112: N = 64 (206 MB) 54 and 48, N = 112 (360 MB) 98 and 105; followed by a
+// kernel that reads y, N = 64: 464 and 476, 126 and 118.
+constexpr unsigned kLastLevelCacheBytes = 256u << 20;
+__device__ __forceinline__ bool stream_stores(const KArgs& a) {
+  return a.y_bytes > kLastLevelCacheBytes && a.N % 16 == 0 && (reinterpret_cast<uintptr_t>(a.y) & 63) == 0;
 }
 
 // Persistent whole tiles, for layers whose reduction is only a few stages
@@ -1519,6 +1540,8 @@ void conv_igemm_f32_pt(KArgs a) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
   };
+  const bool stream = stream_stores(a);
+  auto store = [&]() { store_tile_f32_buf<LAYOUT, C, FUSE>(a, acc, pm0, pn0, wm, wn, hh, q, stream); };
   for (;;) {
     const int next = tile + cnt;
     if (nk > 1) {
@@ -1528,7 +1551,7 @@ void conv_igemm_f32_pt(KArgs a) {
       al.advance(a);
       bl.advance(a);
       issue(cur ^ 1);
-      if (pending) store_tile_f32_buf<LAYOUT, C, FUSE, kStreamAux>(a, acc, pm0, pn0, wm, wn, hh, q);
+      if (pending) store();
       // the stores read acc before it is cleared (else both stay live)
       __builtin_amdgcn_sched_barrier(0);
       clear();
@@ -1561,7 +1584,7 @@ void conv_igemm_f32_pt(KArgs a) {
       issue(cur ^ 1);
     }
     if (nk == 1) {
-      if (pending) store_tile_f32_buf<LAYOUT, C, FUSE, kStreamAux>(a, acc, pm0, pn0, wm, wn, hh, q);
+      if (pending) store();
       __builtin_amdgcn_sched_barrier(0);
       clear();
     }
@@ -1579,7 +1602,7 @@ void conv_igemm_f32_pt(KArgs a) {
     m0 = (tile % a.tiles_m) * MT;
     n0 = (tile / a.tiles_m) * NT;
   }
-  store_tile_f32_buf<LAYOUT, C, FUSE, kStreamAux>(a, acc, pm0, pn0, wm, wn, hh, q);
+  store();
 }
 
 template <int LAYOUT, int AM, int BM, bool FUSE, int TI>

@@ -144,6 +144,29 @@ def test_every_tile_persistent(tile):
                 assert np.array_equal(y, exact), f"{shape} {plan}: not bit-exact"
 
 
+@pytest.mark.parametrize("fused", [False, True])
+def test_persistent_stores_of_an_output_over_the_last_level_cache(fused):
+    """268 MB and more of y in whole 64-byte sectors are stored with the streaming
+    hint, a little less or other sectors without: the same bits as whole tiles."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(77)
+    for N, H, W, K, off in [(16, 256, 257, 64, 0), (16, 256, 256, 64, 0), (20, 230, 230, 64, 0), (16, 256, 257, 64, 4)]:
+        x = torch.randint(-4, 5, (H, W, 4, N), generator=g, device="cuda").float()
+        w = torch.randint(-4, 5, (1, 1, 4, K), generator=g, device="cuda").float()
+        add = torch.randint(-9, 10, (H, W, K, N), generator=g, device="cuda").float() if fused else None
+        out = []
+        for plan in ("tile=64x256,persist=4", "tile=64x256,split=1"):
+            y = torch.full((H * W * K * N + off,), float("nan"), device="cuda")[off:].view(H, W, K, N)
+            if fused:
+                mg3m.conv2d_fwd_f32_fused(x, w, y, add, 1, N, 4, H, W, K, 1, 1, 1, 1, 0, 0, "HWCN", None, 0, plan)
+            else:
+                mg3m.conv2d_fwd_f32_ex(x, w, y, N, 4, H, W, K, 1, 1, 1, 0, "HWCN", None, 0, plan)
+            out.append(y)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]), (N, H, W, K, off)
+
+
+
 @pytest.mark.parametrize("tile", TILES)
 def test_every_tile_nchw_tap_major(tile):
     """NCHW with C a multiple of kt: the filter is copied to [R][S][C][K] in

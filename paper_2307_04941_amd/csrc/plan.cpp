@@ -64,6 +64,11 @@ constexpr double kNchwStridedFactor = 0.6;
 // are faster in place (28x28: 963 against 1005; 56x56, 256 channels, N = 32: 493
 // against 551).
 constexpr double kNchwShortRowFactorB3 = 0.95;
+// HWCN copies of batches under 16 write part of every 64-byte sector: whole
+// sectors' bytes go at these rates, with element stores and with 16-byte ones
+// (384 channels at 112x113, N = 1: 245 us for the copy of 19 MB; 192 at 72x73,
+// N = 4: 29 us for 16 MB).
+constexpr double kPartSectorBytesPerS = 1.1e12, kPartSectorBytesPerS4 = 2.2e12;
 // The resident-filter kernel, against 64x64 tiles of the other on 1x1 layers of
 // 64 to 384 channels: its MFMA efficiency, the filter's way into LDS, and a
 // wave's step of 32 rows alone.  Fitted to which of the two is faster (8x28x28
@@ -84,6 +89,7 @@ constexpr int kB3GroupStages = 12;
 // 11.4 -> 8.1 us).
 constexpr double kB3Small1x1 = 0.63;
 constexpr int kB3WideBatch = 64;
+constexpr double kLastLevelCacheBytes = 256.0 * (1 << 20);
 constexpr double kB3ResStartUs = 2.0, kB3ResEff = 0.75, kB3ResStepUs = 0.6;
 
 long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
@@ -420,7 +426,12 @@ double predict_us(const ConvShape& s, const Plan& p) {
                                       chains * (double)s.Kg / 32 * kB3ResStepUs);
   }
   const double y_bytes = 4.0 * (double)s.Mg * (double)s.Ng;
-  const double xw_bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + (double)s.Kg * s.Mg);
+  // (the resident-filter kernel walks x once per filter tile: from memory each
+  // time where the last-level cache does not hold it; 384 -> 176 channels at 82x82,
+  // N = 120, 1.24 GB: 1237 us, and 916 on fp32 MFMA)
+  const double x_elems = (double)s.N * s.C * s.H * s.W;
+  const double x_passes = p.b3 && p.persist && 4.0 * x_elems > kLastLevelCacheBytes ? p.tiles_m : 1.0;
+  const double xw_bytes = 4.0 * (x_elems * x_passes + (double)s.Kg * s.Mg);
   const double part_bytes =
       (double)tail_pieces(p) * t.mt * t.nt * (p.acc64 ? sizeof(double) : sizeof(float));
   const double t_mem =
@@ -561,6 +572,39 @@ static bool choose_b3(const ConvShape& s, bool x16, bool named, Plan* p) {
   return b3_built(p->b3_load, p->tile);
 }
 
+// Plans of the kernel of bf16 part products that lose to the fp32-MFMA kernels,
+// whatever the two models say (theirs charges the shortest layers a launch and a
+// round, 5 us, which they do in 3).  Counted over 3800 shapes of 1 to 124 images
+// that the models gave to this kernel, both timed (more than 3% between them):
+static bool b3_loses(const ConvShape& s, const Plan& c) {
+  // less than a quarter of a stage: 19 of 19.  (And one product per output is
+  // rounded once on fp32 MFMA, where the part products leave 0.75 ulp.)
+  if (s.Kg < 8) return true;
+  // where the fp32 kernels load single patch elements, not from there on
+  if (c.variant == kVarHwcnVecA || c.variant == kVarHwcnScalar) return false;
+  // one stage, or a second one mostly of padding: 283 of 298, 16 channels at
+  // 14x14, N = 8: 3.0 against 3.9 us.  (24 channels, 1x1, are two of the fp32
+  // kernels' stages, of their slower loader: 24 of 25 the other way.)
+  const bool group24 = s.N % 4 == 0 && s.C % 8 == 0 && s.C % 16 != 0 && s.Kg > 16 && s.Kg <= 32;
+  if (s.Kg <= 48) return !group24;
+  // an address per row, for two or three stages: 13 of 14
+  if (s.Kg <= 96 && s.C % 8 != 0 && s.R * s.S > 1) return true;
+  // 1x1, two to four stages, and little work for most of the chip: 69 of 83, 5 the
+  // other way; 32 -> 256 channels at 56x56, stride 2, N = 4: 4.1 against 4.9 us
+  // (the resident-filter kernel with one filter tile holds its own)
+  if (s.R * s.S == 1 && s.Kg <= 128 && c.dp_tiles + c.tail_wgs > kCUs / 2 && 2.0 * s.Mg * s.Ng * s.Kg < 5e8)
+    return !(c.persist && c.tiles_m == 1);
+  // 16 output channels, small batches, and columns for most of the chip: the fp32
+  // kernels have a tile of 16 rows, 59 of 77, 7 the other way; 128 -> 16 channels,
+  // 3x3 on 64x64, N = 16: 32 against 38 us
+  if (s.K <= 16 && s.N % 4 == 0 && s.N <= 16 && s.C % 16 == 0 && s.sh == 1 && s.sw == 1 && s.Ng >= 100 * 64 && !c.persist)
+    return true;
+  // 24 pieces and more of a stage or two: 172 of 181, 2 the other way; 512 -> 32
+  // channels, 3x3 on 20x20, stride 2, one image: 27 us in 128 pieces, 20 on fp32 MFMA
+  // (and 11 on 16x16 tiles of sixteen waves)
+  return c.split >= 24 && c.tail_wgs > 0 && c.sk_q + (c.sk_r > 0 ? 1 : 0) <= 2;
+}
+
 int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x16, bool w16,
               bool y16, Plan* p, std::string* err, size_t ws_cap) {
   Override o;
@@ -574,6 +618,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
   int best = -1;
   Plan best_plan{};
   size_t least_over_cap = SIZE_MAX;     // smallest workspace among the candidates over ws_cap
+  bool f32_via = false;                 // the best plan of the fp32 kernels runs on HWCN copies
   // the split factors the cost model was calibrated on
   const int splits[] = {2, 3, 4, 6, 8, 16};
   // via: an NCHW call run as HWCN on 16-byte aligned copies of x, w and y in
@@ -588,7 +633,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // which stage through VGPRs
     const bool dma_ok = !c.acc64 && !c.t.m16;
     choose_modes(sv, via || x16, via || w16, via || y16, &c, dma_ok && o.dma != 0);
-    if (c.b3 && !choose_b3(sv, via || x16, o.wm > 0, &c)) return;
+    if (c.b3 && (!choose_b3(sv, via || x16, o.wm > 0, &c) || (o.wm == 0 && b3_loses(sv, c)))) return;
     if (via) {
       auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
       c.via_hwcn = 1;
@@ -614,8 +659,14 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
       return;
     }
     c.est_us = predict_us(sv, c);
-    // the layout changes: x and w in, y out, each read and written once
-    if (via) c.est_us += 2.0 * (double)c.via_bytes / kStreamBytesPerS * 1e6 + 2 * kLaunchUs;
+    // the layout changes: x and w in, y out, each read and written once; x's
+    // copy in runs of N floats, below 16 of them a part of each sector (charged
+    // where the choice is between it and a native plan of the fp32 kernels)
+    if (via) {
+      c.est_us += 2.0 * (double)c.via_bytes / kStreamBytesPerS * 1e6 + 2 * kLaunchUs;
+      if (c.b3 && s.N < 16 && !f32_via)
+        c.est_us += 4.0 * s.C * s.H * s.W * (16 - s.N) / (s.N % 4 == 0 ? kPartSectorBytesPerS4 : kPartSectorBytesPerS) * 1e6;
+    }
     // ties: less workspace traffic, then the larger tile
     const bool better = best < 0 || c.est_us < best_plan.est_us * 0.999 ||
                         (std::fabs(c.est_us - best_plan.est_us) <= best_plan.est_us * 0.001 &&
@@ -682,6 +733,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
   // means the fp32 kernel that it has always meant, if there is one.
   const bool open = !o.mt && !o.wm && !o.kt;
   if (!acc64 && o.dma < 0 && (open || (o.mt && o.wm) || !named_f32)) {
+    f32_via = best >= 0 && best_plan.via_hwcn;
     fam = kB3;
     consider_family();
   }

@@ -129,6 +129,16 @@ def test_b3_keeps_every_bit():
     assert np.array_equal(y[:, :, :, 0].reshape(64, N), wv[0, 0])
 
 
+def test_single_products_are_rounded_once():
+    """One product per output (a channel, 1x1): the fp32 product, bit for bit, as the
+    fp32-MFMA kernels give it; three part products of it would be dropped."""
+    for N in (16, 7, 1):
+        shape = (N, 1, 20, 21, 40, 1, 1, 1, 0)
+        x, w, st, pd = make(shape, 3560 + N, "HWCN")
+        y = run_gpu(x, w, st, pd, "HWCN")
+        assert np.array_equal(y, x[:, :, 0][:, :, None] * w[0, 0, 0][None, None, :, None]), N
+
+
 def _special(kind, x, w):
     x, w = x.copy(), w.copy()
     if kind == "inf":

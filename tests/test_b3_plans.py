@@ -98,3 +98,27 @@ def test_overrides_that_name_fp32_tiles_keep_them(shape, layout):
         assert p["a_mode"] != 3, (plan, p)
     for plan in ("tile=64x64,waves=1x4,kt=32", "tile=64x64,waves=1x4,kt=32,split=2"):
         assert mg3m.conv2d_fwd_f32_plan_info(*shape, layout, plan)["a_mode"] == 3, plan
+
+
+@pytest.mark.parametrize("shape,layout,b3", [
+    ((16, 1, 56, 56, 64, 1, 1, 1, 0), "HWCN", 0), ((7, 7, 30, 30, 40, 1, 1, 1, 0), "HWCN", 0),      # under 8 rows
+    ((7, 8, 30, 30, 40, 1, 1, 1, 0), "HWCN", 1),
+    ((8, 16, 14, 14, 96, 1, 1, 1, 0), "HWCN", 0), ((8, 3, 112, 112, 64, 3, 3, 1, 1), "HWCN", 0),    # a stage, vector loads
+    ((8, 24, 14, 14, 96, 1, 1, 1, 0), "HWCN", 1), ((1, 24, 14, 14, 96, 1, 1, 1, 0), "HWCN", 0), ((7, 16, 14, 14, 96, 1, 1, 1, 0), "HWCN", 1),
+    ((8, 3, 40, 40, 64, 5, 5, 2, 2), "HWCN", 0),                                                      # rows, under three stages
+    ((28, 64, 14, 15, 160, 1, 1, 1, 0), "HWCN", 0), ((64, 64, 56, 56, 256, 1, 1, 1, 0), "HWCN", 1),  # little work, much work
+    ((8, 192, 13, 13, 48, 3, 3, 2, 1), "HWCN", 0), ((3, 512, 7, 7, 48, 3, 3, 1, 1), "HWCN", 1),      # many short pieces
+    ((16, 128, 64, 64, 16, 3, 3, 1, 1), "HWCN", 0), ((32, 128, 64, 64, 16, 3, 3, 1, 1), "HWCN", 1),   # 16 rows
+    ((1, 384, 112, 113, 128, 3, 3, 2, 1), "NCHW", 0), ((32, 128, 57, 57, 128, 3, 3, 2, 1), "NCHW", 1)])   # copies of small batches
+def test_selector_keeps_fp32_mfma_where_it_is_faster(shape, layout, b3):
+    """Both sides of each line that the selector draws between the two kernel families
+    (timed on MI355X), for the caller's call and not for overrides."""
+    assert (mg3m.conv2d_fwd_f32_plan_info(*shape, layout)["a_mode"] == 3) == bool(b3)
+    assert mg3m.conv2d_fwd_f32_plan_info(*shape, "HWCN", "tile=64x64,waves=1x4,kt=32")["a_mode"] == 3
+
+
+def test_resident_filter_not_for_an_x_over_the_last_level_cache():
+    """It walks x once per filter tile, from memory each time there."""
+    big = (120, 384, 82, 82, 176, 1, 1, 1, 0)
+    assert mg3m.conv2d_fwd_f32_plan_info(*big, "HWCN")["persistent"] == 0
+    assert mg3m.conv2d_fwd_f32_plan_info(24, *big[1:], "HWCN")["persistent"] == 1

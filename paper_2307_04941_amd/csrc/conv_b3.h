@@ -22,15 +22,20 @@
 // and is spread between the MFMAs.
 //
 // Range.  bf16 has no bits below 2^-133, so an operand under 2^-110 may have no
-// exact parts; and an infinity has no finite remainder.  What a lost bit is worth
-// depends on the other operand, so the split itself tells: the third part is the
-// upper half of its fp32 value, and a set bit in the lower half is a lost one.
-// A thread that has met one stages NaN for its filter column, so that no sum which
-// that column enters is finite, and marks its wave.  A wave so marked, or with a
-// sum that is not finite, or nonzero and under 2^-86 (part products may have
-// fallen below the fp32 range), computes its sums again on fp32 MFMA.  (One mark
-// for both operands: two take 64x64 tiles over 128 registers, a wave less per
-// SIMD: 72 channels, 3x3 on 56x56, N = 8: 38.6 us, with two 43.0.)
+// exact parts; and an infinity has no finite remainder.  The split itself tells:
+// the third part is the upper half of its fp32 value, and a set bit in the lower
+// half is a lost one.  A wave with a finished sum that is not finite, or nonzero
+// and under 2^-86 (part products may have fallen below the fp32 range), computes
+// its part again on fp32 MFMA, straight from memory.  So does one in whose patches
+// a bit was lost.  Where only the filter lost some (weights that training let
+// decay), they are worth at most Kg * 2^-133 of the largest patch element, and the
+// waves look first whether their sums are above that (least_safe).  The kernels
+// whose waves share a reduction, or keep the filter, stage NaN for a filter column
+// that lost bits instead, so that its sums are computed again (looking takes them
+// 2 and 8% in every call).
+// Time, 512 channels at 28x28, N = 64 (1700 us on fp32 MFMA): 925 us; 1150 with a
+// lost bit in the filter, 1200 with an infinity in x, 3060 where every sum is
+// computed again.  128 -> 512 channels, 1x1 at 28x28, N = 32 (36): 24, 49, 25 and 49.
 #pragma once
 
 #include "conv_kernel.h"
@@ -85,6 +90,16 @@ __device__ __forceinline__ void split2(float a, float b, unsigned (&o)[3], unsig
   lost |= __builtin_bit_cast(unsigned, a) | __builtin_bit_cast(unsigned, b);
 }
 __device__ __forceinline__ bool lost_bits(unsigned lost) { return (unsigned short)lost != 0; }
+
+// The largest of a wave's values, in every lane.
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v = fmaxf(v, __shfl_xor(v, d));
+  return v;
+}
+// The smallest sum of Kg products that lost bits of the filter reach by no more
+// than 2^-25 of it, with patch elements of at most `largest`.
+__device__ __forceinline__ float least_safe(float largest, int Kg) { return largest * ((float)Kg * 0x1p-108f); }
 
 // Formed here, not sunk to the block of their use (the next stage).
 __device__ __forceinline__ void pin3(unsigned (&o)[3], unsigned& lost) {
@@ -404,7 +419,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
     pin3(ap[u][p], lost);
     if (p == C::AR / 2 - 1) {
       // a lost bit, in these rows or met earlier: NaN in their place
-      ap[u][p][0] = lost_bits(lost) ? ~0u : ap[u][p][0];
+      if constexpr (KW > 1) ap[u][p][0] = lost_bits(lost) ? ~0u : ap[u][p][0];
       unsigned* const d = aslot + buf * C::STAGE * 4 + u * (C::T / MT) * C::AR / 8 * MT * 4;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -532,19 +547,24 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
     stage(it, std::integral_constant<int, 0>{});
     if (it + 1 < loops) stage(it + 1, std::integral_constant<int, 1>{});
   }
+  // (the last stage's barrier: the buffers are free)
+  unsigned* const note = reinterpret_cast<unsigned*>(lds0 + KW * C::LDS_CHUNKS) - 16;
+  const bool wave_lost = KW == 1 && __ballot(lost_bits(lost)) != 0;
+  if (KW == 1 && (g4 | q) == 0) note[wn] = wave_lost;
+  // the first group's wave answers for the patches of all groups
+  if (KW > 1 && lost_bits(lost)) lo[0][0][0] = __builtin_nanf("");
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      acc[i][j] += lo[i][j];
+      if (KW > 1 && kg > 0) lds0[((kg - 1) * TM * TN + i * TN + j) * C::T + t] = __builtin_bit_cast(u32x4, acc[i][j]);
+    }
+  static_assert((KW - 1) * TM * TN * C::T <= KW * C::LDS_CHUNKS, "the groups' sums fit the buffers");
+  __syncthreads();
+  // a wave of the work-group has met a lost bit
+  const bool met = KW == 1 && __ballot(q < WN && note[q] != 0) != 0;
   if constexpr (KW > 1) {
-    // the first group's wave answers for the patches of all groups
-    if (lost_bits(lost)) lo[0][0][0] = __builtin_nanf("");
-    // (the last stage's barrier: the buffers are free)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        acc[i][j] += lo[i][j];
-        if (kg > 0) lds0[((kg - 1) * TM * TN + i * TN + j) * C::T + t] = __builtin_bit_cast(u32x4, acc[i][j]);
-      }
-    static_assert((KW - 1) * TM * TN * C::T <= KW * C::LDS_CHUNKS, "the groups' sums fit the buffers");
-    __syncthreads();
     if (kg > 0) return;
 #pragma unroll
     for (int g = 1; g < KW; ++g)
@@ -559,46 +579,82 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      if constexpr (KW == 1) acc[i][j] += lo[i][j];
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         big += __builtin_fabsf(acc[i][j][e]);                    // infinite or NaN if any is
         tiny = min(tiny, __builtin_bit_cast(unsigned, acc[i][j][e]) * 2u - 1u);   // zeros wrap to the maximum
       }
-    }
-  const bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u) | (KW == 1 && lost_bits(lost));
-  if (MG3M_LDS_POISON == 0 && __ballot(again) != 0) {
-    // This wave's part again, on fp32 MFMA, both operands straight from
-    // memory: step k of 32 rows takes rows 8*g + k of each lane group g, the
-    // rows that the lanes' patches hold.
-    clear();
-    start_b(kt00);
-    for (int it = 0; it < nk_all; ++it) {
+  bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u);
+  bool compute = __ballot(again) != 0;
+  if (MG3M_LDS_POISON == 0 && (compute | met)) {
+    // This wave's patches again, straight from memory: with the filter in the
+    // second pass, on fp32 MFMA (step k of 32 rows takes rows 8*g + k of each
+    // lane group g, the rows that the lanes' patches hold); in the first, if that
+    // is not needed anyway, for whether it is.  One loop for both: two take four
+    // registers.
 #pragma unroll 1
-      for (int ks = 0; ks < KS; ++ks) {
-        place_b(true, ks);
+    for (;;) {
+      unsigned lost_b = 0;
+      big = 0.f;
+      if (compute) clear();
+      start_b(kt00);
+      for (int it = 0; it < nk_all; ++it) {
+#pragma unroll 1
+        for (int ks = 0; ks < KS; ++ks) {
+          place_b(true, ks);
 #pragma unroll
-        for (int k = 0; k < ITB; ++k) reload_b(k);
-        // the lane group's first filter row
-        const int row = kRows ? (kt00 + it) * KT + 8 * g4
-                        : kGroups ? (gb.r * a.S + gb.s) * a.C + 8 * gb.g
-                                : (pb.r * a.S + pb.s) * a.C + pb.c0 + 32 * ks + 8 * g4;
-        const unsigned fv = 4u * (unsigned)(row * a.K + m0 + q);
+          for (int k = 0; k < ITB; ++k) reload_b(k);
+          if (!compute) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const bool row_ok = kRows ? row + k < a.Kg : !kGroups || gb.r < a.R;
+            for (int i = 0; i < 8; i += 2)
 #pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            float f[1];
-            bload_w<1>(wr, row_ok & (m0 + i * 16 + q < a.Mg) ? fv + 64u * i : kOOB, (unsigned)k * K4, f);
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[0], fb[k][j], acc[i][j], 0, 0, 0);
+              for (int j = 0; j < TN; ++j) {
+                unsigned o[3];
+                big = fmaxf(big, fmaxf(__builtin_fabsf(fb[i][j]), __builtin_fabsf(fb[i + 1][j])));
+                split2(fb[i][j], fb[i + 1][j], o, lost_b);
+              }
+            continue;
           }
+          // the lane group's first filter row
+          const int row = kRows ? (kt00 + it) * KT + 8 * g4
+                          : kGroups ? (gb.r * a.S + gb.s) * a.C + 8 * gb.g
+                                  : (pb.r * a.S + pb.s) * a.C + pb.c0 + 32 * ks + 8 * g4;
+          const unsigned fv = 4u * (unsigned)(row * a.K + m0 + q);
+          // all loads of the 32 rows in flight at once
+          float f[8][TM][1];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const bool row_ok = kRows ? row + k < a.Kg : !kGroups || gb.r < a.R;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+              bload_w<1>(wr, row_ok & (m0 + i * 16 + q < a.Mg) ? fv + 64u * i : kOOB, (unsigned)k * K4, f[k][i]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[k][i][0], fb[k][j], acc[i][j], 0, 0, 0);
         }
+        advance_b(it + 1 < nk_all);
       }
-      advance_b(it + 1 < nk_all);
+      if (compute) break;
+      const unsigned safe = __builtin_bit_cast(unsigned, least_safe(wave_max(big), a.Kg));
+      again = lost_bits(lost_b) | (tiny < safe * 2u - 1u);
+      // a sum of nothing but lost parts is zero
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            again |= (acc[i][j][e] == 0.f) & (m0 + 16 * i + 4 * g4 + e < a.Mg) &
+                     (n0 + wn * C::WTN + (kVec ? q * TN + j : 16 * j + q) < a.Ng);
+      compute = __ballot(again) != 0;
+      if (!compute) break;
     }
   }
   store(acc, m0, n0, wn * C::WTN, g4, q);

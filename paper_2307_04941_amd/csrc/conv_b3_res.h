@@ -190,17 +190,23 @@ void conv_igemm_b3_res(KArgs a) {
         for (int ks = 0; ks < nk; ++ks) {
           const unsigned fv = 4u * (unsigned)((32 * ks + 8 * g4) * a.K + m0 + q);
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            float xv[TN];
-            bload_w<TN>(xr, v0, C4 * (unsigned)(32 * ks + k), xv);
+          for (int k0 = 0; k0 < 8; k0 += 4) {
+            float xv[4][TN], f[4][TM][1];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-              float f[1];
-              bload_w<1>(wr, m0 + i * 16 + q < a.Mg ? fv + 64u * i : kOOB, (unsigned)k * K4, f);
+            for (int k = 0; k < 4; ++k) {
+              bload_w<TN>(xr, v0, C4 * (unsigned)(32 * ks + k0 + k), xv[k]);
 #pragma unroll
-              for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[0], xv[j], acc[i][j], 0, 0, 0);
+              for (int i = 0; i < TM; ++i)
+                bload_w<1>(wr, m0 + i * 16 + q < a.Mg ? fv + 64u * i : kOOB, (unsigned)(k0 + k) * K4, f[k][i]);
             }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+              for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                  acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[k][i][0], xv[k][j], acc[i][j], 0, 0, 0);
           }
         }
       }

@@ -200,18 +200,27 @@ LOST_FORMS = [((4, 64, 6, 5, 68, 3, 3, 1, 1), "HWCN", "tile=64x128,waves=1x4,kt=
               ((4, 67, 6, 5, 36, 3, 3, 1, 1), "HWCN", "tile=64x64,waves=4x4,kt=32,split=1"),
               ((5, 67, 6, 5, 36, 3, 3, 1, 1), "HWCN", "tile=32x128,waves=1x4,kt=32,split=1"),
               ((4, 128, 41, 52, 68, 1, 1, 1, 0), "HWCN", "tile=64x64,waves=1x2,kt=32")]
-LOST_KINDS = ["x_low", "w_low", "x_sub", "w_sub", "x_one", "w_one", "x_parts_sub", "w_parts_sub"]
+LOST_KINDS = ["x_low", "w_low", "x_sub", "w_sub", "x_one", "w_one", "x_parts_sub", "w_parts_sub", "w_few", "w_few_big"]
 
 
 def _lost(kind, x, w, layout, rng):
     """Finite operands whose bf16 parts do not hold every bit, or barely do."""
     low, high = (w, x) if kind[0] == "w" else (x, w)
+    if layout == "NCHW" and "_few" in kind:
+        w = w.transpose(2, 3, 1, 0)                    # (a view: [R][S][C][K])
     if kind.endswith("_low"):                          # bits below 2^-133, worth 2^-14 of the sums
         low *= np.float32(2.0**-120)
         high *= np.float32(2.0**40)
     elif kind.endswith("parts_sub"):                   # exact in two subnormal parts
         low[...] = rng.integers(-200, 200, low.shape).astype(np.float32) * np.float32(2.0**-133)
         high *= np.float32(2.0**100)
+    elif "_few" in kind:                               # decayed weights, not worth a look or worth one
+        w[..., ::3, :] = rng.integers(1, 1 << 14, w[..., ::3, :].shape).astype(np.float32) * np.float32(2.0**-149)
+        if kind == "w_few_big":                        # whole channels that only they meet
+            few = x[:, :, ::3] if layout == "HWCN" else x[:, ::3]
+            x *= np.float32(2.0**-30)
+            few *= np.float32(2.0**100)
+            few *= np.float32(2.0**50)
     elif kind.endswith("_sub"):                        # no part holds anything
         low *= np.float32(2.0**-136)
     else:                                              # one element; the rest of its tensor zero
@@ -237,6 +246,7 @@ def test_b3_operands_that_lose_bits(form):
         acc, mag = oracle.conv2d(x, w, st, pd, layout)
         say(f"b3 lost bits {kind} {layout} {shape} {plan}")
         y = run_gpu(x, w, st, pd, layout, plan=plan).astype(np.float64)
+        assert np.isfinite(mag).all() and (mag > 0).any(), kind
         err, tol = np.abs(y - acc), 1e-5 * mag + Kg * 2.0**-149
         assert np.all(err <= tol), f"{kind}: worst {float((err / np.maximum(tol, 1e-300)).max()):.3g} of the tolerance"
 

@@ -644,15 +644,19 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
       if (compute) break;
       const unsigned safe = __builtin_bit_cast(unsigned, least_safe(wave_max(big), a.Kg));
       again = lost_bits(lost_b) | (tiny < safe * 2u - 1u);
-      // a sum of nothing but lost parts is zero
+      // a sum of nothing but lost parts is zero (opaque: or its bounds are formed
+      // ahead of the loop, in every call)
+      int rows = a.Mg - m0, cols = a.Ng - n0 - wn * C::WTN;
+      asm volatile("" : "+s"(rows), "+s"(cols));
+      rows -= 4 * g4;
+      cols -= kVec ? q * TN : q;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            again |= (acc[i][j][e] == 0.f) & (m0 + 16 * i + 4 * g4 + e < a.Mg) &
-                     (n0 + wn * C::WTN + (kVec ? q * TN + j : 16 * j + q) < a.Ng);
+            again |= (acc[i][j][e] == 0.f) & (16 * i + e < rows) & ((kVec ? j : 16 * j) < cols);
       compute = __ballot(again) != 0;
       if (!compute) break;
     }

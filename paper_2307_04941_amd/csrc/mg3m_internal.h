@@ -162,8 +162,8 @@ inline constexpr TileDesc kTiles64[kNumTiles64] = {
 constexpr int kNumTilesB3 = 14;
 constexpr int kTileB3Res = 9;
 inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
-    {128, 128, 32, 1, 4, 254, 0.585},                 // 0
-    {128, 256, 32, 1, 8, 244, 0.61},                  // 1: eight waves sharing one filter tile
+    {128, 128, 32, 1, 4, 253, 0.585},                 // 0
+    {128, 256, 32, 1, 8, 243, 0.61},                  // 1: eight waves sharing one filter tile
     {64, 256, 64, 1, 8, 186, 0.50},                   // 2: 64 output channels
     {64, 128, 64, 1, 4, 187, 0.44},                   // 3
     {64, 128, 32, 1, 4, 177, 0.44},                   // 4

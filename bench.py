@@ -51,17 +51,20 @@ def kernel_digest(name: str, launches) -> str:
     return h.hexdigest()[:16]
 
 
-def kernel_name(plan, C: int) -> str:
+B3_FORMS = ["slab", "slab_w", "group", "group_n", "group_c", "row", "row_n"]     # enum B3Load
+
+
+def kernel_name(plan, text: str) -> str:
     """The main kernel's symbol as rocprofv3 prints it (its template arguments:
     layout, filter loader, patch loader, tile rows, columns, depth, waves, and
-    false for the plain output stage the benchmark uses).  C: input channels."""
+    false for the plain output stage the benchmark uses).  text: the plan's
+    string, whose b= names the operand form of the bf16 part products."""
     if plan["a_mode"] == 3:                                               # bf16 part products
         if plan["persistent"]:
             return "void mg3m::conv_igemm_b3_res<false>(mg3m::KArgs)"
-        groups = C % 8 == 0                                               # its operand form (enum B3Load)
-        load = {3: 0, 6: 0, 5: 1, 1: 4, 0: 2 if groups else 5, 2: 3 if groups else 6}[plan["b_mode"]]
-        return (f"void mg3m::conv_igemm_b3<{load}, {plan['mt']}, {plan['nt']}, {plan['kt']}, {plan['waves_n']}, "
-                f"{plan['waves_m']}, false>(mg3m::KArgs)")
+        form = next(f[2:] for f in text.split(",") if f.startswith("b="))
+        return (f"void mg3m::conv_igemm_b3<{B3_FORMS.index(form)}, {plan['mt']}, {plan['nt']}, {plan['kt']}, "
+                f"{plan['waves_n']}, {plan['waves_m']}, false>(mg3m::KArgs)")
     fn = ("conv_igemm_f32_pt" if plan.get("persistent") else          # persistent whole tiles
           "conv_igemm_f32_m16" if plan["mt"] == 16 else "conv_igemm_f32")  # 16-row tiles: 16x16x4 MFMAs
     return (f"void mg3m::{fn}<{plan['layout']}, {plan['a_mode']}, {plan['b_mode']}, "
@@ -351,7 +354,9 @@ def main():
             "bound": "mfma" if ai * HBM_GBS / 1e3 >= peak else "hbm",
             "tile": f"{plan['mt']}x{plan['nt']}x{plan['kt']}", "split": plan["split"],
             "dp_tiles": plan["dp_tiles"], "tail_tiles": plan["tail_tiles"],
-            "grid": plan["grid"], "kernel": kernel_name(plan, L.C),
+            "grid": plan["grid"],
+            "kernel": kernel_name(plan, mg3m.conv2d_fwd_f32_plan_string(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad,
+                                                                         "HWCN", args.plan)),
             "flops": fl, "alg_bytes": by,
         })
         if cold is not None:

@@ -12,7 +12,9 @@
  * size is outH = floor((inH + 2*pad - fltH)/stride) + 1, likewise outW.
  * It is computed as an implicit matrix multiplication (Sec. 4.1.1, Eq. 2,
  * Alg. 1): Mg = OC rows, Ng = B*outH*outW columns, Kg = IC*fltH*fltW depth,
- * on fp32 MFMA, with a per-shape tile / split-K plan standing in for the
+ * on fp32 MFMA or, in most shapes, on bf16 MFMA with every fp32 operand as the
+ * exact sum of three bf16 parts (a product as the six part products that reach
+ * above 2^-24 of it), with a per-shape tile / split-K plan standing in for the
  * paper's multi-grained thread-block mapping (Sec. 4.1.2).
  *
  * Symbols in the argument lists: N = B (batch), C = IC, K = OC, H,W =
@@ -135,8 +137,8 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *                    kt=32), so the tile, waves and kt of a plan string read back
  *                    as an override for the same tile
  *                    Further tiles take fp32 products as bf16 part products, exact in
- *                    both operands (a=vec_m_b3 in plan strings), told apart by their
- *                    waves: 128x128,waves=1x4,kt=32; 128x256,waves=1x8,kt=32;
+ *                    both operands (a=vec_m_b3 in plan strings, b= their operand
+ *                    form), told apart by their waves: 128x128,waves=1x4,kt=32; 128x256,waves=1x8,kt=32;
  *                    64x256,waves=1x8,kt=64; 64x128,waves=1x4,kt=64 and kt=32;
  *                    64x64,waves=1x4,kt=32 and kt=64; 32x128,waves=1x4,kt=32 for
  *                    shapes of the one-tap HWCN loader (HWCN or via=hwcn, N a multiple
@@ -176,7 +178,7 @@ int conv2d_fwd_f32_workspace_bytes(int N, int C, int H, int W, int K, int R, int
  *   sk=<g>           the left-over tiles' k-tiles dealt out to g work-groups in equal
  *                    runs (stream-K); g from the number of left-over tiles to their
  *                    k-tiles in total, else MG3M_ERR_PLAN.  Runs that span two tiles
- *                    need the one-tap HWCN loader (HWCN, N and K multiples of 4, C a
+ *                    need a tile of the bf16 part products, or the one-tap HWCN loader (HWCN, N and K multiples of 4, C a
  *                    multiple of kt, aligned buffers) of this fp32 call and a
  *                    32x32x2-MFMA tile (not 16x64); other
  *                    shapes accept only g that cuts every left-over tile into equal

@@ -17,9 +17,10 @@
 // used because the 32x32x16 form, which reads and writes twice the
 // accumulators per product, ran the chip into its power limit (MFMAs alone on
 // random data: 229 against 372 TFLOPS of fp32 products).  Splitting an operand
-// takes 5.5 vector instructions per element, so the split is done once per
-// work-group for the filter (through LDS) and once per wave for the patches,
-// and is spread between the MFMAs.
+// takes 6 vector instructions per element, half a one of them for the check of
+// lost bits below, so the split is done once per work-group for the filter
+// (through LDS) and once per wave for the patches, and is spread between the
+// MFMAs.
 //
 // Range.  bf16 has no bits below 2^-133, so an operand under 2^-110 may have no
 // exact parts; and an infinity has no finite remainder.  The split itself tells:

@@ -69,10 +69,6 @@ constexpr double kNchwShortRowFactorB3 = 0.95;
 // (384 channels at 112x113, N = 1: 245 us for the copy of 19 MB; 192 at 72x73,
 // N = 4: 29 us for 16 MB).
 constexpr double kPartSectorBytesPerS = 1.1e12, kPartSectorBytesPerS4 = 2.2e12;
-// The resident-filter kernel, against 64x64 tiles of the other on 1x1 layers of
-// 64 to 384 channels: its MFMA efficiency, the filter's way into LDS, and a
-// wave's step of 32 rows alone.  Fitted to which of the two is faster (8x28x28
-// columns, 128 -> 512 channels: 11.8 against 13.8 us; 320 -> 320: 21.1 against 15.4).
 // What a latency-bound launch of the bf16 part product kernel takes less than
 // the model's launch and round (a graph of them: 2.7 us apart from its chain).
 constexpr double kB3AloneUs = 2.0;
@@ -90,6 +86,10 @@ constexpr int kB3GroupStages = 12;
 constexpr double kB3Small1x1 = 0.63;
 constexpr int kB3WideBatch = 64;
 constexpr double kLastLevelCacheBytes = 256.0 * (1 << 20);
+// The resident-filter kernel, against 64x64 tiles of the other on 1x1 layers of
+// 64 to 384 channels: its MFMA efficiency, the filter's way into LDS, and a
+// wave's step of 32 rows alone.  Fitted to which of the two is faster (8x28x28
+// columns, 128 -> 512 channels: 11.8 against 13.8 us; 320 -> 320: 21.1 against 15.4).
 constexpr double kB3ResStartUs = 2.0, kB3ResEff = 0.75, kB3ResStepUs = 0.6;
 
 long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
@@ -766,6 +766,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
 std::string plan_to_string(const ConvShape& s, const Plan& p) {
   static const char* an[] = {"vec_m", "vec_k", "scalar", "vec_m_b3"};
   static const char* bn[] = {"vec_n", "vec_c", "scalar", "vec_n_tap", "vec_w", "vec_w_tap", "vec_n_tap_dma"};
+  static const char* fn[] = {"slab", "slab_w", "group", "group_n", "group_c", "row", "row_n"};   // by B3Load
   static const char* en[] = {"elem", "vec_m"};
   char buf[512];
   std::snprintf(buf, sizeof buf,
@@ -774,7 +775,7 @@ std::string plan_to_string(const ConvShape& s, const Plan& p) {
                 "Mg=%lld,Ng=%lld,Kg=%lld",
                 p.acc64 ? "acc=f64," : "", p.via_hwcn ? "via=hwcn," : "",
                 p.persist ? "persist," : "", p.t.mt, p.t.nt, p.t.wm, p.t.wn, p.t.kt, p.split, p.dp_tiles, p.tail_tiles, p.tail_wgs, p.grid,
-                p.tiles_m, p.tiles_n, p.k_tiles, an[p.a_mode], bn[p.b_mode], en[p.e_mode],
+                p.tiles_m, p.tiles_n, p.k_tiles, an[p.a_mode], p.b3 ? fn[p.b3_load] : bn[p.b_mode], en[p.e_mode],
                 p.lds_bytes, p.ws_bytes, p.pad_eff, p.est_us, s.Mg, s.Ng, s.Kg);
   return buf;
 }

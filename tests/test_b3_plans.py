@@ -7,6 +7,8 @@ import re
 
 import pytest
 
+import bench
+import workloads
 from paper_2307_04941_amd import build, mg3m
 
 RES = "tile=64x64,waves=1x2,kt=32"
@@ -122,3 +124,20 @@ def test_resident_filter_not_for_an_x_over_the_last_level_cache():
     big = (120, 384, 82, 82, 176, 1, 1, 1, 0)
     assert mg3m.conv2d_fwd_f32_plan_info(*big, "HWCN")["persistent"] == 0
     assert mg3m.conv2d_fwd_f32_plan_info(24, *big[1:], "HWCN")["persistent"] == 1
+
+
+def test_benchmark_names_built_kernels():
+    """The kernel that the benchmark says a layer runs is one of the build's, by its
+    operand form (b= of the plan's string)."""
+    with open(build.RESOURCES) as f:
+        built = set(json.load(f))
+    for name in ("vgg16_n64", "resnet50_n32"):
+        for L in workloads.workload(name):
+            args = (L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad, "HWCN")
+            kernel = bench.kernel_name(mg3m.conv2d_fwd_f32_plan_info(*args), mg3m.conv2d_fwd_f32_plan_string(*args))
+            assert kernel in built, (L.name, kernel)
+    for shape, form in [((8, 72, 9, 9, 64, 3, 3, 1, 1), "group"), ((7, 72, 9, 9, 64, 3, 3, 1, 1), "group_n"),
+                        ((1, 72, 9, 9, 64, 3, 3, 1, 1), "group_c"), ((8, 75, 9, 9, 64, 3, 3, 1, 1), "row"),
+                        ((7, 75, 9, 9, 64, 3, 3, 1, 1), "row_n"), ((8, 64, 9, 9, 64, 3, 3, 1, 1), "slab")]:
+        text = mg3m.conv2d_fwd_f32_plan_string(*shape, "HWCN", "tile=64x64,waves=1x4,kt=32")
+        assert f",b={form}," in text, (shape, text)

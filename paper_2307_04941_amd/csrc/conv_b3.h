@@ -30,10 +30,11 @@
 // its part again on fp32 MFMA, straight from memory.  So does one in whose patches
 // a bit was lost.  Where only the filter lost some (weights that training let
 // decay), they are worth at most Kg * 2^-133 of the largest patch element, and the
-// waves look first whether their sums are above that (least_safe).  The kernels
-// whose waves share a reduction, or keep the filter, stage NaN for a filter column
-// that lost bits instead, so that its sums are computed again (looking takes them
-// 2 and 8% in every call).
+// waves of the largest tiles (eight side by side) look first whether their sums
+// are above that (least_safe).  The others stage NaN for a filter column that lost
+// bits instead, so that its sums are computed again: the barrier and the code for
+// the look take 2% of the smaller tiles' time in every call, and 8% of the
+// resident-filter kernel's; of the largest tiles' none to 1%.
 // Time, 512 channels at 28x28, N = 64 (1700 us on fp32 MFMA): 925 us; 1150 with a
 // lost bit in the filter, 1200 with an infinity in x, 3060 where every sum is
 // computed again.  128 -> 512 channels, 1x1 at 28x28, N = 32 (36): 24, 49, 25 and 49.
@@ -242,6 +243,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
   constexpr int TM = C::TM, TN = C::TN, KS = C::KS;
   constexpr bool kGroups = b3_groups(LD), kRows = b3_rows(LD), kVec = b3_vec(LD);   // kGroups: kRows too
   constexpr int NB = kVec ? 1 : TN;      // patch addresses per lane
+  constexpr bool kLook = KW == 1 && WN == 8;      // lost bits of the filter: look before computing again
   static_assert(!kGroups || (KS == 1 && C::UA == 1), "one group of eight rows, or a part of it, per thread");
   // this group's stages: nk of them from kt0; every group runs `loops`, as the
   // barriers are common
@@ -420,7 +422,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
     pin3(ap[u][p], lost);
     if (p == C::AR / 2 - 1) {
       // a lost bit, in these rows or met earlier: NaN in their place
-      if constexpr (KW > 1) ap[u][p][0] = lost_bits(lost) ? ~0u : ap[u][p][0];
+      if constexpr (!kLook) ap[u][p][0] = lost_bits(lost) ? ~0u : ap[u][p][0];
       unsigned* const d = aslot + buf * C::STAGE * 4 + u * (C::T / MT) * C::AR / 8 * MT * 4;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -550,8 +552,8 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
   }
   // (the last stage's barrier: the buffers are free)
   unsigned* const note = reinterpret_cast<unsigned*>(lds0 + KW * C::LDS_CHUNKS) - 16;
-  const bool wave_lost = KW == 1 && __ballot(lost_bits(lost)) != 0;
-  if (KW == 1 && (g4 | q) == 0) note[wn] = wave_lost;
+  const bool wave_lost = kLook && __ballot(lost_bits(lost)) != 0;
+  if (kLook && (g4 | q) == 0) note[wn] = wave_lost;
   // the first group's wave answers for the patches of all groups
   if (KW > 1 && lost_bits(lost)) lo[0][0][0] = __builtin_nanf("");
 #pragma unroll
@@ -562,9 +564,9 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
       if (KW > 1 && kg > 0) lds0[((kg - 1) * TM * TN + i * TN + j) * C::T + t] = __builtin_bit_cast(u32x4, acc[i][j]);
     }
   static_assert((KW - 1) * TM * TN * C::T <= KW * C::LDS_CHUNKS, "the groups' sums fit the buffers");
-  __syncthreads();
+  if constexpr (KW > 1 || kLook) __syncthreads();
   // a wave of the work-group has met a lost bit
-  const bool met = KW == 1 && __ballot(q < WN && note[q] != 0) != 0;
+  const bool met = kLook && __ballot(q < WN && note[q] != 0) != 0;
   if constexpr (KW > 1) {
     if (kg > 0) return;
 #pragma unroll
@@ -586,7 +588,7 @@ __device__ __forceinline__ void tile_product_b3(const KArgs& a, u32x4* lds0, int
         big += __builtin_fabsf(acc[i][j][e]);                    // infinite or NaN if any is
         tiny = min(tiny, __builtin_bit_cast(unsigned, acc[i][j][e]) * 2u - 1u);   // zeros wrap to the maximum
       }
-  bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u);
+  bool again = !(big < __builtin_inff()) | (tiny < kB3TinyBits * 2u - 1u) | (KW == 1 && !kLook && lost_bits(lost));
   bool compute = __ballot(again) != 0;
   if (MG3M_LDS_POISON == 0 && (compute | met)) {
     // This wave's patches again, straight from memory: with the filter in the

@@ -165,11 +165,11 @@ inline constexpr TileDesc kTilesB3[kNumTilesB3] = {
     {128, 128, 32, 1, 4, 253, 0.585},                 // 0
     {128, 256, 32, 1, 8, 243, 0.61},                  // 1: eight waves sharing one filter tile
     {64, 256, 64, 1, 8, 186, 0.50},                   // 2: 64 output channels
-    {64, 128, 64, 1, 4, 187, 0.44},                   // 3
-    {64, 128, 32, 1, 4, 177, 0.44},                   // 4
+    {64, 128, 64, 1, 4, 186, 0.44},                   // 3
+    {64, 128, 32, 1, 4, 179, 0.44},                   // 4
     {64, 64, 32, 1, 4, 113, 0.62, 0, 0, 0.60},        // 5
     {64, 64, 64, 1, 4, 122, 0.372},                   // 6
-    {32, 128, 32, 1, 4, 133, 0.37},                   // 7: small layers
+    {32, 128, 32, 1, 4, 131, 0.37},                   // 7: small layers
     {64, 256, 32, 1, 8, 187, 0.50},                   // 8: as 2, for the forms of 32-deep stages only
     {64, 64, 32, 1, 2, 162, 0.50},                    // 9: the resident-filter kernel (1x1, persistent)
     {64, 64, 32, 4, 4, 116, 0.62, 0, 0, 0.60},        // 10: wm groups of waves share the reduction out (few tiles)

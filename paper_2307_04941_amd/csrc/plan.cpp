@@ -618,6 +618,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
   int best = -1;
   Plan best_plan{};
   size_t least_over_cap = SIZE_MAX;     // smallest workspace among the candidates over ws_cap
+  const bool open = !o.mt && !o.wm && !o.kt;      // the override, if any, leaves the kernel open
   bool f32_via = false;                 // the best plan of the fp32 kernels runs on HWCN copies
   // the split factors the cost model was calibrated on
   const int splits[] = {2, 3, 4, 6, 8, 16};
@@ -633,7 +634,7 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
     // which stage through VGPRs
     const bool dma_ok = !c.acc64 && !c.t.m16;
     choose_modes(sv, via || x16, via || w16, via || y16, &c, dma_ok && o.dma != 0);
-    if (c.b3 && (!choose_b3(sv, via || x16, o.wm > 0, &c) || (o.wm == 0 && b3_loses(sv, c)))) return;
+    if (c.b3 && (!choose_b3(sv, via || x16, o.wm > 0, &c) || (open && b3_loses(sv, c)))) return;
     if (via) {
       auto r256 = [](size_t b) { return (b + 255) / 256 * 256; };
       c.via_hwcn = 1;
@@ -731,7 +732,6 @@ int make_plan(const ConvShape& s, const char* override_text, bool acc64, bool x1
   // The kernels of bf16 part products are the selector's to choose, or named by
   // tile and waves together.  An override that names less (a tile, a depth, dma=)
   // means the fp32 kernel that it has always meant, if there is one.
-  const bool open = !o.mt && !o.wm && !o.kt;
   if (!acc64 && o.dma < 0 && (open || (o.mt && o.wm) || !named_f32)) {
     f32_via = best >= 0 && best_plan.via_hwcn;
     fam = kB3;

@@ -102,6 +102,16 @@ def test_overrides_that_name_fp32_tiles_keep_them(shape, layout):
         assert mg3m.conv2d_fwd_f32_plan_info(*shape, layout, plan)["a_mode"] == 3, plan
 
 
+@pytest.mark.parametrize("layout", ["HWCN", "NCHW"])
+@pytest.mark.parametrize("shape,plan", [((60, 128, 27, 8, 32, 1, 1, 1, 0), "tile=64x64,kt=64"),
+                                        ((24, 64, 22, 15, 208, 1, 1, 1, 0), "tile=64x64,kt=64"),
+                                        ((60, 64, 25, 30, 64, 1, 1, 1, 0), "tile=64x256,kt=64")])
+def test_overrides_that_only_part_products_fit_run_where_they_are_slower(shape, plan, layout):
+    """No fp32 tile has this depth: the rules that prefer the fp32-MFMA kernels on
+    short reductions choose between kernels and do not refuse a named one."""
+    assert mg3m.conv2d_fwd_f32_plan_info(*shape, layout, plan)["a_mode"] == 3
+
+
 @pytest.mark.parametrize("shape,layout,b3", [
     ((16, 1, 56, 56, 64, 1, 1, 1, 0), "HWCN", 0), ((7, 7, 30, 30, 40, 1, 1, 1, 0), "HWCN", 0),      # under 8 rows
     ((7, 8, 30, 30, 40, 1, 1, 1, 0), "HWCN", 1),
